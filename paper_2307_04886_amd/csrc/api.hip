@@ -336,45 +336,6 @@ bool options_ok(const gmg_options& o) {
          o.block_min_rows >= 0 && (o.autotune == 0 || o.autotune == 1);
 }
 
-// The single-workgroup tail of a cycle: levels tail_start.. with their views
-// and the LDS offsets of their arrays (batched layout: make_tail_batched).
-template <class V>
-void make_tail_at(const Handle& h, const Cycle<V>& c, int start, TailDescT<V>& t) {
-  const int nl = (int)h.L.size();
-  t = TailDescT<V>();
-  t.nlev = nl - start;
-  t.nu_pre = h.opt.nu_pre;
-  t.nu_post = h.opt.nu_post;
-  t.descending_post = c.symmetric ? 1 : 0;
-  t.cinv = h.cinv;
-  int64_t off = 0;
-  auto take = [&](int64_t bytes) {
-    const int32_t o = (int32_t)off;
-    off += (bytes + 15) & ~(int64_t)15;
-    return o;
-  };
-  for (int l = start; l < nl; ++l) {
-    const LevelViewT<V>& v = c.v[l];
-    const int i = l - start;
-    t.lv[i] = v;
-    const bool coarsest = l + 1 == nl;
-    t.o_x[i] = take(((int64_t)v.n + (coarsest ? 0 : 1)) * sizeof(V));
-    t.o_b[i] = take((int64_t)v.n * sizeof(V));
-    if (!coarsest) {
-      t.o_r[i] = take(((int64_t)v.n + 1) * sizeof(V));
-      t.o_c[i] = take((int64_t)v.ncolors * 16);
-      t.o_w[i] = take((int64_t)v.n * 2);
-    }
-  }
-  if (off > kTailLdsMax) throw Error{GMG_DEVICE_ERROR, "tail LDS layout exceeds its budget"};
-  t.lds_bytes = (int32_t)off;
-}
-
-template <class V>
-void make_tail(const Handle& h, Cycle<V>& c) {
-  make_tail_at(h, c, h.tail_start, c.tail);
-}
-
 struct PT {
   int32_t* rp = nullptr;
   int32_t* col = nullptr;
@@ -516,24 +477,14 @@ void build(Handle& h, int64_t n, const double* points, int64_t m, const int32_t*
       h.L[l].nnzP = vals[3 + 3 * l];
     }
   }
-  // levels with few rows run their part of the V-cycle in one workgroup
-  // (the coarsest level always; above it while the levels are small and their
-  // arrays fit the LDS of one workgroup, counted in double)
+  // levels with few rows are swept by one workgroup (tail.hip)
   h.tail_start = nl - 1;
-  int64_t tail_bytes = tail_lds_bytes(h.L[nl - 1].n, 0, true, 8);
-  while (h.tail_start > 0 && h.L[h.tail_start - 1].n <= kTailRows && nl - (h.tail_start - 1) <= kMaxTail) {
-    const Level& up = h.L[h.tail_start - 1];
-    const int64_t more = tail_lds_bytes(up.n, (int64_t)up.color_ptr.size() - 1, false, 8);
-    if (tail_bytes + more > kTailLdsMax) break;
-    tail_bytes += more;
-    --h.tail_start;
-  }
-  for (int l = ell_first_level(h); l + 1 < nl; ++l) ell_layout(h, h.L[l], h.L[l + 1]);
+  while (h.tail_start > 0 && h.L[h.tail_start - 1].n <= kTailRows) --h.tail_start;
+  for (int l = h.tail_start; l + 1 < nl; ++l) tail_layout(h, h.L[l], h.L[l].view.R);
   autotune(h);
   h.plain.v.clear();
   for (int l = 0; l < nl; ++l) h.plain.v.push_back(h.L[l].view);
   h.plain.symmetric = false;
-  make_tail(h, h.plain);
   sync(s, "build");
   cache_settle(s);
 }
@@ -542,40 +493,82 @@ void build(Handle& h, int64_t n, const double* points, int64_t m, const int32_t*
 // zero guess, prolong and correct the pre-relaxed iterate, post-relax.  In a
 // symmetric cycle the post-relaxation visits the colours in descending order.
 // Rows of level l whose first pre-smoothing update the restriction into l
-// performs (its first colour; 0 when level l is solved by the tail kernel or
-// has no pre-smoothing).
+// performs (its first colour; 0 on the coarsest level or without pre-smoothing).
 int32_t folded_rows(const Handle& h, size_t l) {
   const Level& lv = h.L[l];
-  if ((int)l >= h.tail_start || h.opt.nu_pre < 1 || lv.color_ptr.size() < 2) return 0;
+  if (l + 1 == h.L.size() || h.opt.nu_pre < 1 || lv.color_ptr.size() < 2) return 0;
   return lv.color_ptr[1];
 }
+
+// The coarsest solve of a cycle, x_c = A_c^-1 b_c; with fine given (and the
+// coarsest level small enough) b_c = P^T r is formed by the same kernel.
+inline bool coarse_fuses(const Handle& h) { return h.L.back().n <= kCoarseFused; }
+
+template <class V>
+CoarseJob<V> coarse_job(const Handle& h, const LevelViewT<V>* fine, const LevelViewT<V>& c, int32_t stride) {
+  CoarseJob<V> J;
+  J.n = c.n;
+  J.rows = coarse_rows(c.n);
+  J.stride = stride;
+  J.M = h.cinv;
+  if (fine) {
+    J.T = fine->T;
+    J.r = fine->r;
+    J.nf = fine->n;
+    J.staged = (int64_t)fine->n * (int64_t)sizeof(V) <= kCoarseStaged ? 1 : 0;
+  }
+  J.b = c.b;
+  J.x = c.x;
+  return J;
+}
+
+template <class V>
+void coarse_correction(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s);
 
 template <class V>
 void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const LevelViewT<V>& v = c.v[l];
-  if ((int)l == h.tail_start) {
-    if (c.tail.nlev == 1) coarse_solve(h.cinv, v, s); else tail_vcycle(c.tail, s);
+  if (l + 1 == h.L.size()) {
+    coarse_fused(coarse_job<V>(h, nullptr, v, 1), 1, s);
     return;
   }
-  const LevelViewT<V>& cv = c.v[l + 1];
   const Level& lv = h.L[l];
   const bool timed = !c.symmetric;            // the solve's cycle is the measured one
   // on a coarse level the restriction into it already did the first colour
   const int skip = l > 0 && folded_rows(h, l) > 0 ? 1 : 0;
-  for (int k = 0; k < h.opt.nu_pre; ++k) gs_sweep(v, lv, s, l == 0, false, timed, k == 0 ? skip : 0);
-  residual(v, s, l == 0);
-  restrict_to(v, cv, s, folded_rows(h, l + 1));
+  const bool tail = (int)l >= h.tail_start;
+  if (tail) {
+    tail_sweeps(tail_pre_job(v, 1, h.opt.nu_pre, skip), tail_width(v.maxa), 1, s);
+  } else {
+    for (int k = 0; k < h.opt.nu_pre; ++k) gs_sweep(v, lv, s, l == 0, false, timed, k == 0 ? skip : 0);
+    residual(v, s, l == 0);
+  }
+  coarse_correction(h, c, l, s);
+  const LevelViewT<V>& cv = c.v[l + 1];
+  if (tail) {
+    tail_sweeps(tail_post_job(v, cv, 1, h.opt.nu_post, c.symmetric), tail_width(v.maxa), 1, s);
+  } else {
+    prolong_correct(v, cv, s);
+    for (int k = 0; k < h.opt.nu_post; ++k) gs_sweep(v, lv, s, l == 0, c.symmetric, timed);
+  }
+}
+
+// The cycle below level l: its residual restricted, the next level solved.
+template <class V>
+void coarse_correction(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
+  if (l + 2 == h.L.size() && coarse_fuses(h)) {
+    coarse_fused(coarse_job<V>(h, &c.v[l], c.v[l + 1], 1), 1, s);
+    return;
+  }
+  restrict_to(c.v[l], c.v[l + 1], s, folded_rows(h, l + 1));
   vcycle(h, c, l + 1, s);
-  prolong_correct(v, cv, s);
-  for (int k = 0; k < h.opt.nu_post; ++k) gs_sweep(v, lv, s, l == 0, c.symmetric, timed);
 }
 
 // The part of the level-0 V-cycle between pre- and post-smoothing.
 void cycle_inner(Handle& h, hipStream_t s) {
   const Cycle<double>& c = h.plain;
   residual(c.v[0], s, true);
-  restrict_to(c.v[0], c.v[1], s, folded_rows(h, 1));
-  vcycle(h, c, 1, s);
+  coarse_correction(h, c, 0, s);
   prolong_correct(c.v[0], c.v[1], s);
 }
 
@@ -679,7 +672,6 @@ void kry_prepare(Handle& h, Cycle<double>& c) {
   c.symmetric = true;
   c.v[0].b = h.kry.r;
   c.v[0].x = h.kry.z;
-  make_tail(h, c);
 }
 
 // The float cycle: float copies of every level's A_l, P_l^T, P_l and diagonal
@@ -718,22 +710,9 @@ void kry_prepare(Handle& h, Cycle<float>& c) {
       f.q_val = to_f32_copy(h, d.q_val, (int64_t)3 * d.n, s);
       if (d.B.nblk > 0)                      // block sweep: same layout, float values
         f.B = d.B.with_values(to_f32_copy(h, d.B.elv, lv.blk_entries, s));
-      if (d.e_cinfo) {                       // a tail level
-        f.e_cinfo = d.e_cinfo;
-        f.e_ww = d.e_ww;
-        f.e_col_gs = d.e_col_gs;
-        f.e_col = d.e_col;
-        f.e_tcol = d.e_tcol;
-        f.e_wt = d.e_wt;
-        f.e_slots = d.e_slots;
-        f.e_tslots = d.e_tslots;
-        f.e_val_gs = to_f32_copy(h, d.e_val_gs, lv.e_slots, s);
-        f.e_val = to_f32_copy(h, d.e_val, lv.e_slots, s);
-        f.e_tval = to_f32_copy(h, d.e_tval, lv.e_tslots, s);
-      }
+      if (d.R.col) tail_layout(h, lv, f.R);  // swept by one workgroup
     }
   }
-  make_tail(h, c);
 }
 
 template <class V>
@@ -862,30 +841,6 @@ int pcg(Handle& h, double nb, double tol, int32_t max_iters, hipStream_t s, int3
 }
 
 // ------------------------------------------------------------------ batched right-hand sides
-// The single-workgroup tail of a batched cycle: as make_tail, iterates of
-// n * kBatch elements.
-// LDS places of the batched tail's iterates, level by level while they fit.
-template <class V>
-void place_batched_tail(TailDescT<V>& t) {
-  const int32_t cap = kTailLdsBytes / (int32_t)sizeof(V);
-  t.lds_elems = 0;
-  for (int l = 0; l < t.nlev; ++l) {
-    const int32_t e = t.lv[l].n * kBatch;
-    if (t.lds_elems + e <= cap) {
-      t.lds_off[l] = t.lds_elems;
-      t.lds_elems += e;
-    } else {
-      t.lds_off[l] = -1;
-    }
-  }
-}
-
-template <class V>
-void make_tail_batched(const Handle& h, Cycle<V>& c) {
-  make_tail(h, c);
-  place_batched_tail(c.tail);
-}
-
 void bat_alloc(Handle& h) {
   Batch& k = h.bat;
   if (k.x) return;
@@ -913,7 +868,6 @@ void bat_prepare(Handle& h, Cycle<V>& c, const Cycle<V>& single) {
     c.v[0].b = (V*)h.bat.r;
     c.v[0].x = (V*)h.bat.z;
   }
-  make_tail_batched(h, c);
 }
 
 template <class V>
@@ -941,18 +895,31 @@ Cycle<V>& bat_ready(Handle& h) {
 template <class V>
 void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const LevelViewT<V>& v = c.v[l];
-  if ((int)l == h.tail_start) {
-    if (c.tail.nlev == 1) mcoarse(h.cinv, v, s); else mtail(c.tail, s);
+  if (l + 1 == h.L.size()) {
+    coarse_fused(coarse_job<V>(h, nullptr, v, kBatch), kBatch, s);
     return;
   }
   const LevelViewT<V>& cv = c.v[l + 1];
   const Level& lv = h.L[l];
-  for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false);
-  mresidual(v, s);
-  mrestrict(v, cv, s);
-  mvcycle(h, c, l + 1, s);
-  mprolong(v, cv, s);
-  for (int k = 0; k < h.opt.nu_post; ++k) mgs_sweep(v, lv, s, c.symmetric);
+  const bool tail = (int)l >= h.tail_start;
+  if (tail) {
+    tail_sweeps(tail_pre_job(v, kBatch, h.opt.nu_pre, 0), tail_width(v.maxa), kBatch, s);
+  } else {
+    for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false);
+    mresidual(v, s);
+  }
+  if (l + 2 == h.L.size() && coarse_fuses(h)) {
+    coarse_fused(coarse_job<V>(h, &v, cv, kBatch), kBatch, s);
+  } else {
+    mrestrict(v, cv, s);
+    mvcycle(h, c, l + 1, s);
+  }
+  if (tail) {
+    tail_sweeps(tail_post_job(v, cv, kBatch, h.opt.nu_post, c.symmetric), tail_width(v.maxa), kBatch, s);
+  } else {
+    mprolong(v, cv, s);
+    for (int k = 0; k < h.opt.nu_post; ++k) mgs_sweep(v, lv, s, c.symmetric);
+  }
 }
 
 template <class V>
@@ -1129,7 +1096,6 @@ void precondition_noalloc(Handle& h, const double* r, double* z, int32_t precisi
       h.noalloc64.symmetric = true;
       h.noalloc64.v[0].b = sr;
       h.noalloc64.v[0].x = sr + kNoAllocMaxPoints;
-      make_tail(h, h.noalloc64);
       h.noalloc_base = sr;
     }
     const Cycle<double>& c = h.noalloc64;
@@ -1174,9 +1140,11 @@ struct RowStep {
   const J* djobs = nullptr;
   const GTile* dtiles = nullptr;
   void add(const J& j, int32_t member, int64_t elements) {
+    add_tiles(j, member, (elements + kBlock - 1) / kBlock);
+  }
+  void add_tiles(const J& j, int32_t member, int64_t nt) {
     const int32_t job = (int32_t)jobs.size();
     jobs.push_back(j);
-    const int64_t nt = (elements + kBlock - 1) / kBlock;
     for (int64_t t = 0; t < nt; ++t) tiles.push_back(GTile{job, (int32_t)t, member, 0});
   }
   void upload(DeviceTables& d) {
@@ -1189,7 +1157,7 @@ struct RowStep {
 template <class V>
 struct GroupPlan {
   // the cycle as a sequence of steps, in launch order
-  enum Kind { SWEEP, RESIDUAL, RESTRICT, PROLONG, GEMV, TAIL };
+  enum Kind { SWEEP, RESIDUAL, RESTRICT, PROLONG, TAIL, COARSE };
   struct Step {
     Kind kind;
     int32_t index;
@@ -1199,12 +1167,23 @@ struct GroupPlan {
   std::vector<RowStep<GResJob<V>>> residuals;
   std::vector<RowStep<GRestJob<V>>> restricts;
   std::vector<RowStep<GProlJob<V>>> prolongs;
-  RowStep<GGemvJob<V>> gemv;
-  std::vector<TailDescT<V>> tails;
-  std::vector<int32_t> tail_members;
-  const TailDescT<V>* dtails = nullptr;
-  const int32_t* dtail_members = nullptr;
-  int32_t tail_lds = 0;
+  // one-workgroup levels: the members' jobs of one row width
+  struct TailStep {
+    std::vector<TailJob<V>> jobs;
+    std::vector<int32_t> members;
+    int32_t W = 0;
+    int32_t nchunk = 0;
+    size_t lds = 0;
+    const TailJob<V>* djobs = nullptr;
+    const int32_t* dmembers = nullptr;
+  };
+  std::vector<TailStep> tails;
+  // coarsest solves: the members' jobs of one number of rows a workgroup takes
+  struct CoarseStep : RowStep<CoarseJob<V>> {
+    int32_t rows = 0;
+    size_t lds = 0;
+  };
+  std::vector<CoarseStep> coarse;
   // CG: one job per member, tiles over each member's n * kBatch elements
   RowStep<GKryJob<V>> kry;
   int32_t count = 0;
@@ -1215,27 +1194,55 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
   const int M = (int)H.size();
   P.count = M;
   std::vector<Cycle<V>*> C(M);
-  // Each member's tail starts where all of its levels' iterates fit the
-  // batched tail's LDS (the levels above it run as grouped launches, with the
-  // same arithmetic as in the tail): one workgroup then carries only small
-  // levels, and the group waits for the slowest member's tail once per cycle.
+  // Members' levels solved by separate launches are grouped from the finest
+  // down (levels below ts), their one-workgroup levels from the coarsest up, so
+  // that these and the coarsest solves of members of different depth share
+  // their launches.
   std::vector<int> ts(M);
-  int Lmax = 0, pre = 0, post = 0;
+  int Lmax = 0, Tmax = 0, pre = 0, post = 0;
   for (int m = 0; m < M; ++m) {
     const Handle& h = *H[m];
     C[m] = &bat_ready<V>(*H[m]);
-    const int nl = (int)h.L.size();
-    int start = nl - 1;
-    int64_t elems = h.L[nl - 1].n * kBatch;
-    while (start > h.tail_start && elems + h.L[start - 1].n * kBatch <= kTailLdsBytes / (int64_t)sizeof(V)) {
-      elems += h.L[start - 1].n * kBatch;
-      --start;
-    }
-    ts[m] = start;
-    Lmax = std::max(Lmax, start);
+    ts[m] = h.tail_start;
+    Lmax = std::max(Lmax, ts[m]);
+    Tmax = std::max(Tmax, (int)h.L.size() - 1 - ts[m]);
     pre = std::max(pre, h.opt.nu_pre);
     post = std::max(post, h.opt.nu_post);
   }
+  auto add_restrict = [&](RowStep<GRestJob<V>>& rt, int m, int l) {
+    const Handle& h = *H[m];
+    if (l + 2 == (int)h.L.size() && coarse_fuses(h)) return;      // the coarsest solve restricts
+    const LevelViewT<V>& v = C[m]->v[l];
+    const LevelViewT<V>& cv = C[m]->v[l + 1];
+    rt.add(GRestJob<V>{v.T, v.r, cv.b, cv.x, cv.n}, m, (int64_t)cv.n * kBatch);
+  };
+  auto push_restrict = [&](RowStep<GRestJob<V>>&& rt) {
+    if (rt.ntiles() == 0) return;
+    P.order.push_back({GroupPlan<V>::RESTRICT, (int32_t)P.restricts.size()});
+    P.restricts.push_back(std::move(rt));
+  };
+  // the one-workgroup levels d above the coarsest, one step per row width
+  auto tail_step = [&](int d, bool is_post) {
+    for (int32_t W : {8, 16, kTailWMax}) {
+      typename GroupPlan<V>::TailStep st;
+      st.W = W;
+      for (int m = 0; m < M; ++m) {
+        const Handle& h = *H[m];
+        const int l = (int)h.L.size() - 1 - d;
+        if (l < ts[m]) continue;
+        const LevelViewT<V>& v = C[m]->v[l];
+        if (tail_width(v.maxa) != W) continue;
+        st.jobs.push_back(is_post ? tail_post_job(v, C[m]->v[l + 1], kBatch, h.opt.nu_post, true)
+                                  : tail_pre_job(v, kBatch, h.opt.nu_pre, 0));
+        st.members.push_back(m);
+        st.nchunk = std::max(st.nchunk, v.R.nchunk);
+        st.lds = std::max(st.lds, tail_lds_bytes(v.R, v.n, C[m]->v[l + 1].n));
+      }
+      if (st.jobs.empty()) continue;
+      P.order.push_back({GroupPlan<V>::TAIL, (int32_t)P.tails.size()});
+      P.tails.push_back(std::move(st));
+    }
+  };
   auto classes = [&](int m, int l) { return (int)H[m]->L[l].color_ptr.size() - 1; };
   auto sweep_step = [&](int l, int sweep, bool descending) {
     int kmax = 0;
@@ -1266,32 +1273,37 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
     for (int m = 0; m < M; ++m) {
       if (l >= ts[m]) continue;
       const LevelViewT<V>& v = C[m]->v[l];
-      const LevelViewT<V>& cv = C[m]->v[l + 1];
       rs.add(GResJob<V>{v.A, v.b, v.x, v.r, v.n}, m, (int64_t)v.n * kBatch);
-      rt.add(GRestJob<V>{v.T, v.r, cv.b, cv.x, cv.n}, m, (int64_t)cv.n * kBatch);
+      add_restrict(rt, m, l);
     }
     P.order.push_back({GroupPlan<V>::RESIDUAL, (int32_t)P.residuals.size()});
     P.residuals.push_back(std::move(rs));
-    P.order.push_back({GroupPlan<V>::RESTRICT, (int32_t)P.restricts.size()});
-    P.restricts.push_back(std::move(rt));
+    push_restrict(std::move(rt));
   }
-  for (int m = 0; m < M; ++m) {
-    const Handle& h = *H[m];
-    const Cycle<V>& c = *C[m];
-    if (ts[m] + 1 == (int)h.L.size()) {
-      const LevelViewT<V>& v = c.v[ts[m]];
-      P.gemv.add(GGemvJob<V>{h.cinv, v.b, v.x, v.n}, m, (int64_t)v.n * kBatch);
-    } else {
-      TailDescT<V> t;
-      make_tail_at(h, c, ts[m], t);
-      place_batched_tail(t);
-      P.tails.push_back(t);
-      P.tail_members.push_back(m);
-      P.tail_lds = std::max(P.tail_lds, t.lds_elems * (int32_t)sizeof(V));
+  for (int d = Tmax; d >= 1; --d) {
+    tail_step(d, false);
+    RowStep<GRestJob<V>> rt;
+    for (int m = 0; m < M; ++m)
+      if ((int)H[m]->L.size() - 1 - d >= ts[m]) add_restrict(rt, m, (int)H[m]->L.size() - 1 - d);
+    push_restrict(std::move(rt));
+  }
+  for (int32_t rows : {16, 8, 4, 2}) {
+    typename GroupPlan<V>::CoarseStep st;
+    st.rows = rows;
+    for (int m = 0; m < M; ++m) {
+      const Handle& h = *H[m];
+      const int nl = (int)h.L.size();
+      const LevelViewT<V>& cv = C[m]->v[nl - 1];
+      if (coarse_rows(cv.n) != rows) continue;
+      const CoarseJob<V> J = coarse_job<V>(h, nl > 1 && coarse_fuses(h) ? &C[m]->v[nl - 2] : nullptr, cv, kBatch);
+      st.add_tiles(J, m, (cv.n + rows - 1) / rows);
+      st.lds = std::max(st.lds, coarse_lds(J));
     }
+    if (st.ntiles() == 0) continue;
+    P.order.push_back({GroupPlan<V>::COARSE, (int32_t)P.coarse.size()});
+    P.coarse.push_back(std::move(st));
   }
-  P.order.push_back({GroupPlan<V>::TAIL, 0});
-  P.order.push_back({GroupPlan<V>::GEMV, 0});
+  for (int d = 1; d <= Tmax; ++d) tail_step(d, true);
   for (int l = Lmax - 1; l >= 0; --l) {
     RowStep<GProlJob<V>> pr;
     for (int m = 0; m < M; ++m) {
@@ -1316,10 +1328,12 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
   for (auto& st : P.residuals) st.upload(dt);
   for (auto& st : P.restricts) st.upload(dt);
   for (auto& st : P.prolongs) st.upload(dt);
-  P.gemv.upload(dt);
+  for (auto& st : P.coarse) st.upload(dt);
   P.kry.upload(dt);
-  P.dtails = dt.put(P.tails);
-  P.dtail_members = dt.put(P.tail_members);
+  for (auto& st : P.tails) {
+    st.djobs = dt.put(st.jobs);
+    st.dmembers = dt.put(st.members);
+  }
 }
 
 // One CG iteration of every member with active[m] != 0 (bat_iteration).
@@ -1348,12 +1362,16 @@ void group_iteration(const GroupPlan<V>& P, const int32_t* active, hipStream_t s
         gprolong(r.djobs, r.dtiles, r.ntiles(), active, s);
         break;
       }
-      case GroupPlan<V>::GEMV:
-        ggemv(P.gemv.djobs, P.gemv.dtiles, P.gemv.ntiles(), active, s);
+      case GroupPlan<V>::TAIL: {
+        const auto& t = P.tails[st.index];
+        gtail_sweeps(t.djobs, t.dmembers, (int32_t)t.jobs.size(), t.W, t.nchunk, t.lds, active, s);
         break;
-      case GroupPlan<V>::TAIL:
-        gtail(P.dtails, P.dtail_members, (int32_t)P.tails.size(), P.tail_lds, active, s);
+      }
+      case GroupPlan<V>::COARSE: {
+        const auto& c = P.coarse[st.index];
+        gcoarse_fused(c.djobs, c.dtiles, c.ntiles(), c.rows, c.lds, active, s);
         break;
+      }
     }
   }
   gkry_direction(P.kry.djobs, P.count, P.kry.dtiles, P.kry.ntiles(), active, s);
@@ -1812,7 +1830,7 @@ int gmg_update_matrix(gmg_handle hh, const double* A_val_dev, void* stream) {
       refresh_values(*h, h->L[l]);
       block_values(*h, h->L[l]);
     }
-    for (int l = ell_first_level(*h); l + 1 < nl; ++l) ell_values(*h, h->L[l]);
+    for (int l = h->tail_start; l + 1 < nl; ++l) tail_layout(*h, h->L[l], h->L[l].view.R);
     coarse_factor(*h, h->L[nl - 1]);                 // also raises the flags of the steps above
     if (h->kry.ready[1])
       for (int l = 0; l + 1 < nl; ++l) {
@@ -1821,10 +1839,7 @@ int gmg_update_matrix(gmg_handle hh, const double* A_val_dev, void* stream) {
         to_f32(d.A.val, (float*)f.A.val, h->L[l].a_slots, s);
         to_f32(d.diag, (float*)f.diag, d.n, s);
         if (d.B.nblk > 0) to_f32(d.B.elv, (float*)f.B.elv, h->L[l].blk_entries, s);
-        if (d.e_cinfo) {
-          to_f32(d.e_val_gs, (float*)f.e_val_gs, h->L[l].e_slots, s);
-          to_f32(d.e_val, (float*)f.e_val, h->L[l].e_slots, s);
-        }
+        if (d.R.col) tail_layout(*h, h->L[l], f.R);
       }
     sync(s, "update");
   } catch (const Error& e) {

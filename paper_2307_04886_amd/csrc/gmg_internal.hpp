@@ -158,9 +158,11 @@ inline int blocks_for(int64_t n, int per_block = kBlock) {
 }
 
 // ------------------------------------------------------------------ hierarchy layout
-constexpr int kTailThreads = 1024;   // one workgroup runs the V-cycle below kTailRows
-constexpr int64_t kTailRows = 4096;
-constexpr int kMaxTail = 8;
+constexpr int64_t kTailRows = 4096;  // levels of at most this many rows are swept by one workgroup
+constexpr int kTailT = 512;          // its threads
+constexpr int kTailWMax = 32;        // entries of a row it holds at most
+constexpr int64_t kCoarseFused = 1024;   // coarsest rows up to which the restriction is fused with the solve
+constexpr int64_t kCoarseStaged = 72 * 1024;   // residual bytes it keeps in LDS beside the inverse's columns (at most 73 KiB)
 constexpr int kLaneEntries = 8;      // entries per lane per pass of a lane-parallel row
 
 // A matrix in SELL-64: entry t of row r at ptr[r/64] + 64 t + r%64.
@@ -247,6 +249,21 @@ struct BlockView {
   }
 };
 
+// A_l of a level swept by one workgroup (tail.hip): every colour's rows in
+// chunks of kWave, a row per lane, W = tail_width(longest row) entries.  Entry e
+// of lane t's row in chunk q has its column, as a byte offset into a vector of
+// V, at ((q W/8 + e/8) kWave + t) 8 + e%8 and its value, in blocks of E = 16
+// bytes, at ((q W/E + e/E) kWave + t) E + e%E.  The diagonal and the padding
+// have column n (a zero behind the iterate).
+template <class V>
+struct TailRows {
+  int32_t nchunk = 0;
+  const int4* chunk = nullptr;          // first row, rows, colour, entries of the longest row (a multiple of 8, at most W)
+  const int32_t* info = nullptr;        // [n] row length << 8 | entry of the diagonal (255: past the first W)
+  const uint16_t* col = nullptr;
+  const V* val = nullptr;
+};
+
 // What the V-cycle kernels need of one level (device pointers, new numbering),
 // with values and vectors in V (double; float for the mixed-precision cycle).
 template <class V>
@@ -273,87 +290,60 @@ struct LevelViewT {
   V* x = nullptr;
   V* b = nullptr;
   V* r = nullptr;
-  // Levels of the single-workgroup tail (not the coarsest): A_l in per-colour
-  // blocked ELL
-  // (colour c: rows [lo, hi), width w a multiple of kTailGroup, element
-  // offset off; entry positions from ell_col_index / ell_val_index), once with
-  // its diagonal (residual) and once without (Gauss-Seidel: the diagonal's
-  // column is n, its value 0), and P_l^T likewise as one segment of n_c rows
-  // and width e_wt.  Padding entries have column n and value 0: the tail keeps
-  // a zero at x[n] and r[n], so that every padded term is +0 and leaves the sum
-  // unchanged.
-  // A tail level's rows are sorted within each colour by length, longest
-  // first, and e_ww[r] is the width (entries, a multiple of 4) of the longest
-  // row among the 64 rows of r's wavefront (64-row chunks from the colour's
-  // first row): a wavefront loads only that many entries of its rows.
-  const int32_t* e_cinfo = nullptr;     // [ncolors][4]: lo, hi, w, off
-  const uint16_t* e_ww = nullptr;
-  const int32_t* e_col_gs = nullptr;
-  const V* e_val_gs = nullptr;
-  const int32_t* e_col = nullptr;
-  const V* e_val = nullptr;
-  const int32_t* e_tcol = nullptr;
-  const V* e_tval = nullptr;
-  int32_t e_wt = 0;
-  int32_t e_slots = 0, e_tslots = 0;    // entries of the ELL arrays of A_l / P_l^T
+  TailRows<V> R;                        // levels swept by one workgroup (not the coarsest)
   BlockView<V> B;                       // block sweep of a level swept in block order
 };
 using LevelView = LevelViewT<double>;
 
+// One call of the one-workgroup sweeps of a level (tail.hip), for one or
+// several interleaved vectors (stride apart).
 template <class V>
-struct TailDescT {
-  int32_t nlev = 0;                     // tail levels, the last one is the coarsest
-  int32_t nu_pre = 0, nu_post = 0;
-  int32_t descending_post = 0;          // 1: post-smoothing visits the colours in descending order
-  // single-vector tail: byte offsets in LDS of every tail level's x (n + 1),
-  // b (n), r (n + 1) and colour table (the coarsest level: x and b)
-  int32_t lds_bytes = 0;
-  int32_t o_x[kMaxTail] = {}, o_b[kMaxTail] = {}, o_r[kMaxTail] = {}, o_c[kMaxTail] = {}, o_w[kMaxTail] = {};
-  // batched tail: LDS (elements of V) holding the tail levels' iterates
-  int32_t lds_elems = 0;
-  int32_t lds_off[kMaxTail] = {};       // offset of level l's x in LDS, or -1 (global)
-  const double* cinv = nullptr;
-  LevelViewT<V> lv[kMaxTail];
+struct TailJob {
+  int32_t n = 0, ncolors = 0, stride = 1, nsweeps = 0;
+  int32_t skip = 0;                     // colours of the first sweep already done
+  int32_t descending = 0;
+  int32_t maxlen = 0;
+  TailRows<V> A;
+  Sell<V> S;                            // A_l again: the entries of rows longer than the buffers
+  const V* diag = nullptr;
+  const V* b = nullptr;
+  V* x = nullptr;
+  V* r = nullptr;                       // set: the residual after the sweeps
+  const int32_t* q_col = nullptr;       // set: x += P x_c before them
+  const V* q_val = nullptr;
+  const int32_t* q_cnt = nullptr;
+  const V* xc = nullptr;
+  int32_t nc = 0;
 };
-constexpr int32_t kTailLdsBytes = 96 * 1024;      // batched tail
-constexpr int32_t kTailLdsMax = 144 * 1024;       // single-vector tail (gfx950: 160 KiB per workgroup)
-constexpr int kTailGroup = 8;                     // tail ELL widths are multiples of this
+
+// The coarsest solve, fused with the restriction P^T r when T is set (else b
+// is given); `rows` rows of the solution per workgroup (a power of two).
+template <class V>
+struct CoarseJob {
+  int32_t n = 0, rows = 0, stride = 1;
+  int32_t nf = 0, staged = 0;           // length of r; 1: it fits the LDS (kCoarseStaged bytes)
+  const double* M = nullptr;            // the inverse by columns, stride inv_ld(n)
+  Sell<V> T;
+  const V* r = nullptr;
+  const V* b = nullptr;
+  V* x = nullptr;
+};
 
 // Row stride of the dense coarsest inverse: n rounded up to even, so that two
 // consecutive entries of a row are one 16-byte aligned load.
 inline __host__ __device__ int64_t inv_ld(int64_t n) { return (n + 1) & ~(int64_t)1; }
-
-// Element index of entry t of row r in a tail ELL segment (first row lo, cnt
-// rows, element offset off): columns in blocks of 4 entries per row, values in
-// blocks of 2 (one 16-byte load per block and lane).
-inline __host__ __device__ int64_t ell_col_index(int64_t off, int64_t cnt, int64_t lo, int64_t r, int64_t t) {
-  return off + (t >> 2) * (cnt * 4) + (r - lo) * 4 + (t & 3);
-}
-inline __host__ __device__ int64_t ell_val_index(int64_t off, int64_t cnt, int64_t lo, int64_t r, int64_t t) {
-  return off + (t >> 1) * (cnt * 2) + (r - lo) * 2 + (t & 1);
-}
-
-// LDS bytes of one level in the single-vector tail (value type V): x and r with
-// their zero, b, the colour table and the rows' wavefront widths; the coarsest
-// level keeps x and b only.  Arrays start on 16-byte boundaries.
-inline int64_t tail_lds_bytes(int64_t n, int64_t ncolors, bool coarsest, int64_t vbytes) {
-  auto up = [](int64_t b) { return (b + 15) & ~(int64_t)15; };
-  if (coarsest) return 2 * up(n * vbytes);
-  return 2 * up((n + 1) * vbytes) + up(n * vbytes) + up(ncolors * 16) + up(n * 2);
-}
 
 // Rows of a level with at most kTailRows rows are sorted within each colour by
 // their width in 4-entry quads (longest first; kLenKeys classes, longer rows
 // share the last), then by index.
 constexpr int kLenKeys = 32;
 
-// One variant of the V-cycle: its per-level views and its tail descriptor.
+// One variant of the V-cycle: its per-level views.
 // symmetric: post-smoothing runs the colours in descending order, so that the
 // cycle from a zero guess is a symmetric operator (a CG preconditioner).
 template <class V>
 struct Cycle {
   std::vector<LevelViewT<V>> v;
-  TailDescT<V> tail;
   bool symmetric = false;
 };
 
@@ -416,9 +406,6 @@ struct Level {
   int32_t* t_col = nullptr;
   double* t_val = nullptr;
   int32_t galerkin_hs = 1024;           // hash slots of the numeric Galerkin pass (3/4 hold the longest row)
-  // tail levels: the per-colour ELL of A_l and the ELL of P_l^T (LevelViewT)
-  std::vector<int32_t> e_cinfo_h;       // host copy of view.e_cinfo
-  int64_t e_slots = 0, e_tslots = 0;
 };
 
 // Preconditioned conjugate gradients (double) around a symmetric V-cycle in
@@ -476,7 +463,7 @@ struct Handle {
   double* red = nullptr;                // reduction partials
   double* norm_host = nullptr;          // pinned: the solve's residual norm, written by the cycle's last kernel
   double* norm_dev = nullptr;           // its device address
-  int tail_start = -1;                  // first level solved by the single-workgroup tail kernel
+  int tail_start = -1;                  // first level swept by one workgroup (the coarsest at the latest)
   Cycle<double> plain;                  // the V-cycle of the solve (Alg. 2)
   Cycle<double> noalloc64;              // the symmetric double cycle on the no-allocation scratch
   const double* noalloc_base = nullptr; // scratch address noalloc64 was made for
@@ -574,9 +561,10 @@ void solve_layout(Handle& h, Level& lv, const Level* nx, const int32_t* t_rp, co
                   const double* t_val);
 void coarse_factor(Handle& h, Level& lv);
 void refresh_values(Handle& h, Level& lv);                 // SELL values and diagonal from lv.aval
-void ell_layout(Handle& h, Level& lv, const Level& nx);    // blocked ELL of A_l and P_l^T (view.e_*)
-void ell_values(Handle& h, Level& lv);                     // blocked ELL values of A_l from its SELL
-int ell_first_level(const Handle& h);                      // levels ell_first_level.. (not the coarsest) have it
+// A_l of a level swept by one workgroup in the layout of its chunks, from its
+// SELL copy; R: the arrays to write (allocated when empty)
+template <class V>
+void tail_layout(Handle& h, const Level& lv, TailRows<V>& R);
 
 // ------------------------------------------------------------------ launchers (solve.hip)
 // V-cycle phases on one level, for V = double and V = float.  gs_sweep visits
@@ -595,10 +583,6 @@ template <class V>
 void restrict_to(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s, int32_t first = 0);
 template <class V>
 void prolong_correct(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
-template <class V>
-void coarse_solve(const double* cinv, const LevelViewT<V>& c, hipStream_t s);
-template <class V>
-void tail_vcycle(const TailDescT<V>& d, hipStream_t s);
 template <class V>
 void fill_zero(V* p, int64_t n, hipStream_t s);
 void to_f32(const double* src, float* dst, int64_t n, hipStream_t s);
@@ -621,10 +605,6 @@ template <class V>
 void mrestrict(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
 template <class V>
 void mprolong(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
-template <class V>
-void mcoarse(const double* cinv, const LevelViewT<V>& c, hipStream_t s);
-template <class V>
-void mtail(const TailDescT<V>& d, hipStream_t s);
 void mkry_init(Batch& k, int64_t n, hipStream_t s);
 template <class V>
 void mkry_direction(Batch& k, const V* z, int64_t n, hipStream_t s);
@@ -679,13 +659,6 @@ struct GProlJob {                       // x += P x_c
   int64_t n;
 };
 template <class V>
-struct GGemvJob {                       // x = A_c^-1 b
-  const double* M;
-  const V* b;
-  V* x;
-  int64_t n;
-};
-template <class V>
 struct GKryJob {                        // a member's CG state (level 0, double) and cycle ends
   SellView A0;
   double *x, *b, *r, *r_old, *p, *q, *part, *scal;
@@ -702,12 +675,33 @@ template <class V>
 void grestrict(const GRestJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
 template <class V>
 void gprolong(const GProlJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
+// one-workgroup levels (tail.hip)
+int32_t tail_width(int32_t maxlen);                        // entries W held of rows of at most maxlen
 template <class V>
-void ggemv(const GGemvJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
-// one workgroup per listed member: descs[i] is member members[i]'s tail
+size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc);
+// nu sweeps (the first `skip` colours of the first one done), then the residual
 template <class V>
-void gtail(const TailDescT<V>* descs, const int32_t* members, int32_t count, int32_t lds_bytes, const int32_t* active,
-           hipStream_t s);
+TailJob<V> tail_pre_job(const LevelViewT<V>& v, int32_t stride, int32_t nu, int32_t skip);
+// x += P x_c, then nu sweeps
+template <class V>
+TailJob<V> tail_post_job(const LevelViewT<V>& v, const LevelViewT<V>& c, int32_t stride, int32_t nu, bool descending);
+template <class V>
+void tail_sweeps(const TailJob<V>& J, int32_t W, int32_t vectors, hipStream_t s);
+// kBatch vectors of every listed member (jobs[i] is member members[i]'s; all of width W, at most nchunk chunks)
+template <class V>
+void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t W, int32_t nchunk, size_t lds,
+                  const int32_t* active, hipStream_t s);
+int32_t coarse_rows(int64_t n);
+template <class V>
+size_t coarse_lds(const CoarseJob<V>& J);
+template <class V>
+void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s);
+// tiles: groups of `rows` rows of every member's job (all jobs of J.rows == rows)
+template <class V>
+void gcoarse_fused(const CoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, int32_t rows, size_t lds,
+                   const int32_t* active, hipStream_t s);
+template <class V>
+void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s);
 // CG steps over the members' jobs (count of them); `tiles` cover each member's n * kBatch elements
 template <class V>
 void gkry_init(const GKryJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);

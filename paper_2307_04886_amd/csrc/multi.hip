@@ -115,103 +115,6 @@ __global__ void __launch_bounds__(kBlock) k_mprolong(LevelViewT<V> L, const V* _
   mprolong_entry(L.q_col, L.q_val, L.q_cnt, L.n, xc, x, t);
 }
 
-// x = A_c^-1 b for the K right-hand sides, in double, as the single-vector
-// coarse solve: entry (i, q) is the sum over k ascending of (A_c^-1 e_k)_i b_kq.
-template <class V>
-__device__ __forceinline__ void mgemv_entry(const double* M, const V* b, V* x, int64_t n, int64_t t) {
-  const int64_t i = t / K;
-  const int q = (int)(t % K);
-  double acc = 0.0;
-  const int64_t ld = inv_ld(n);
-  // the loads of eight terms are issued before they are added (in ascending k)
-  int64_t k = 0;
-  for (; k + 8 <= n; k += 8) {
-    double m[8], v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      m[u] = M[(k + u) * ld + i];
-      v[u] = (double)b[(k + u) * K + q];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc = acc + m[u] * v[u];
-  }
-  for (; k < n; ++k) acc = acc + M[k * ld + i] * (double)b[k * K + q];
-  x[t] = (V)acc;
-}
-
-template <class V>
-__global__ void __launch_bounds__(kBlock) k_mgemv(const double* __restrict__ M, const V* __restrict__ b,
-                                                  V* __restrict__ x, int64_t n) {
-  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= n * K) return;
-  mgemv_entry(M, b, x, n, t);
-}
-
-// The tail of the cycle in one workgroup (as k_tail_vcycle), one lane per
-// (row, right-hand side); iterates in LDS where they fit.
-template <class V>
-__device__ __forceinline__ void mtail_gs(const LevelViewT<V>& L, V* X, bool descending) {
-  for (int k = 0; k < L.ncolors; ++k) {
-    const int c = descending ? L.ncolors - 1 - k : k;
-    const int32_t r0 = L.cptr[c], r1 = L.cptr[c + 1];
-    for (int64_t t = threadIdx.x; t < (int64_t)(r1 - r0) * K; t += kTailThreads) {
-      const int32_t r = r0 + (int32_t)(t / K);
-      const int q = (int)(t % K);
-      const V acc = row_sum_multi(L.A, r, (const V*)X, r, q);
-      X[(int64_t)r * K + q] = (L.b[(int64_t)r * K + q] - acc) / L.diag[r];
-    }
-    __syncthreads();
-  }
-}
-
-template <class V>
-__device__ __forceinline__ void mtail_run(const TailDescT<V>& d) {
-  extern __shared__ double lds_raw[];
-  V* lds = reinterpret_cast<V*>(lds_raw);
-  const int tid = threadIdx.x;
-  auto X = [&](int l) -> V* { return d.lds_off[l] >= 0 ? lds + d.lds_off[l] : d.lv[l].x; };
-  if (d.lds_off[0] >= 0)
-    for (int64_t i = tid; i < (int64_t)d.lv[0].n * K; i += kTailThreads) X(0)[i] = d.lv[0].x[i];
-  __syncthreads();
-  for (int l = 0; l + 1 < d.nlev; ++l) {
-    const LevelViewT<V>& L = d.lv[l];
-    V* XL = X(l);
-    for (int s = 0; s < d.nu_pre; ++s) mtail_gs(L, XL, false);
-    for (int64_t t = tid; t < (int64_t)L.n * K; t += kTailThreads)
-      L.r[t] = L.b[t] - row_sum_multi(L.A, (int32_t)(t / K), (const V*)XL, -1, (int)(t % K));
-    __syncthreads();
-    const LevelViewT<V>& C = d.lv[l + 1];
-    V* XC = X(l + 1);
-    for (int64_t t = tid; t < (int64_t)C.n * K; t += kTailThreads) {
-      C.b[t] = row_sum_multi(L.T, (int32_t)(t / K), (const V*)L.r, -1, (int)(t % K));
-      XC[t] = V(0);
-    }
-    __syncthreads();
-  }
-  {
-    const LevelViewT<V>& C = d.lv[d.nlev - 1];
-    V* XC = X(d.nlev - 1);
-    for (int64_t t = tid; t < (int64_t)C.n * K; t += kTailThreads) mgemv_entry(d.cinv, (const V*)C.b, XC, C.n, t);
-    __syncthreads();
-  }
-  for (int l = d.nlev - 2; l >= 0; --l) {
-    const LevelViewT<V>& L = d.lv[l];
-    V* XL = X(l);
-    const V* XC = X(l + 1);
-    for (int64_t t = tid; t < (int64_t)L.n * K; t += kTailThreads)
-      mprolong_entry(L.q_col, L.q_val, L.q_cnt, L.n, XC, XL, t);
-    __syncthreads();
-    for (int s = 0; s < d.nu_post; ++s) mtail_gs(L, XL, d.descending_post != 0);
-  }
-  if (d.lds_off[0] >= 0)
-    for (int64_t i = tid; i < (int64_t)d.lv[0].n * K; i += kTailThreads) d.lv[0].x[i] = X(0)[i];
-}
-
-template <class V>
-__global__ void __launch_bounds__(kTailThreads) k_mtail(TailDescT<V> d) {
-  mtail_run(d);
-}
-
 // ------------------------------------------------------------ CG, K right-hand sides
 // Per-block partial sums by right-hand side: with a grid stride that is a
 // multiple of K, thread t always handles right-hand side t mod K; lanes of a
@@ -498,25 +401,6 @@ __global__ void __launch_bounds__(kBlock) k_gprolong(const GProlJob<V>* __restri
 }
 
 template <class V>
-__global__ void __launch_bounds__(kBlock) k_ggemv(const GGemvJob<V>* __restrict__ jobs,
-                                                  const GTile* __restrict__ tiles, const int32_t* __restrict__ active) {
-  const GTile g = tiles[blockIdx.x];
-  if (!active[g.member]) return;
-  const GGemvJob<V> J = jobs[g.job];
-  const int64_t t = (int64_t)g.tile * kBlock + threadIdx.x;
-  if (t >= J.n * K) return;
-  mgemv_entry(J.M, J.b, J.x, J.n, t);
-}
-
-template <class V>
-__global__ void __launch_bounds__(kTailThreads) k_gtail(const TailDescT<V>* __restrict__ descs,
-                                                        const int32_t* __restrict__ members,
-                                                        const int32_t* __restrict__ active) {
-  if (!active[members[blockIdx.x]]) return;
-  mtail_run(descs[blockIdx.x]);
-}
-
-template <class V>
 __global__ void __launch_bounds__(kBlock) k_gkry_init(const GKryJob<V>* __restrict__ jobs,
                                                       const GTile* __restrict__ tiles,
                                                       const int32_t* __restrict__ active) {
@@ -662,16 +546,6 @@ void mprolong(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s) {
   k_mprolong<V><<<blocks_for((int64_t)v.n * K), kBlock, 0, s>>>(v, c.x, v.x);
 }
 
-template <class V>
-void mcoarse(const double* cinv, const LevelViewT<V>& c, hipStream_t s) {
-  k_mgemv<V><<<blocks_for(c.n * K), kBlock, 0, s>>>(cinv, c.b, c.x, c.n);
-}
-
-template <class V>
-void mtail(const TailDescT<V>& d, hipStream_t s) {
-  k_mtail<V><<<1, kTailThreads, (size_t)d.lds_elems * sizeof(V), s>>>(d);
-}
-
 void mkry_init(Batch& k, int64_t n, hipStream_t s) {
   k_mkry_init<<<blocks_for(n * K), kBlock, 0, s>>>(k.p, k.r_old, n * K, k.scal);
 }
@@ -732,17 +606,6 @@ void gprolong(const GProlJob<V>* jobs, const GTile* tiles, int32_t ntiles, const
 }
 
 template <class V>
-void ggemv(const GGemvJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s) {
-  if (ntiles > 0) k_ggemv<V><<<ntiles, kBlock, 0, s>>>(jobs, tiles, active);
-}
-
-template <class V>
-void gtail(const TailDescT<V>* descs, const int32_t* members, int32_t count, int32_t lds_bytes, const int32_t* active,
-           hipStream_t s) {
-  if (count > 0) k_gtail<V><<<count, kTailThreads, (size_t)lds_bytes, s>>>(descs, members, active);
-}
-
-template <class V>
 void gkry_init(const GKryJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s) {
   if (ntiles > 0) k_gkry_init<V><<<ntiles, kBlock, 0, s>>>(jobs, tiles, active);
 }
@@ -791,8 +654,6 @@ void ggather_scalars(const GKryJob<V>* jobs, int32_t count, int which, uint64_t*
   template void gresidual<V>(const GResJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
   template void grestrict<V>(const GRestJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);         \
   template void gprolong<V>(const GProlJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
-  template void ggemv<V>(const GGemvJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);             \
-  template void gtail<V>(const TailDescT<V>*, const int32_t*, int32_t, int32_t, const int32_t*, hipStream_t); \
   template void gkry_init<V>(const GKryJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
   template void gcycle_start<V>(const GKryJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);       \
   template void gkry_direction<V>(const GKryJob<V>*, int32_t, const GTile*, int32_t, const int32_t*,          \
@@ -810,8 +671,6 @@ GMG_INSTANTIATE_GROUPED(float)
   template void mresidual<V>(const LevelViewT<V>&, hipStream_t);                                \
   template void mrestrict<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);          \
   template void mprolong<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);           \
-  template void mcoarse<V>(const double*, const LevelViewT<V>&, hipStream_t);                   \
-  template void mtail<V>(const TailDescT<V>&, hipStream_t);                                     \
   template void mkry_direction<V>(Batch&, const V*, int64_t, hipStream_t);                      \
   template void mscatter<V>(const int32_t*, const V*, int64_t, int, double*, hipStream_t);
 GMG_INSTANTIATE_MULTI(double)

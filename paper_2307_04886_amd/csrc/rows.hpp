@@ -52,6 +52,42 @@ __device__ __forceinline__ V row_sum_seq(const Sell<V>& A, int32_t r, const V* x
   return acc;
 }
 
+// A row's place in its slice: first entry, entries, and the slice's width.
+struct SellRow {
+  int32_t base, len, width;
+};
+template <class V>
+__device__ __forceinline__ SellRow sell_row(const Sell<V>& A, int32_t r) {
+  const int32_t p0 = A.ptr[r / kSlice], p1 = A.ptr[r / kSlice + 1];
+  return SellRow{p0 + (r & (kSlice - 1)), A.len[r], (p1 - p0) / kSlice};
+}
+
+// The same sum over all entries of a row, for one of several interleaved
+// vectors (x's entry j at j * stride).  The loads past a row's end stay in the
+// slice (its padding, column 0), at the entry the other rows of the wavefront
+// read: a load whose lanes each re-read their own last entry touches as many
+// cache lines as there are short rows, and costs the load path that many cycles.
+template <int CH, class V, class X>
+__device__ __forceinline__ V row_sum_at(const Sell<V>& A, SellRow R, X x, int32_t stride) {
+  V acc = V(0);
+  for (int32_t t0 = 0; t0 < R.width; t0 += CH) {
+    int32_t j[CH];
+    V v[CH], xv[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int32_t o = R.base + min(t0 + u, R.width - 1) * kSlice;
+      j[u] = A.col[o];
+      v[u] = A.val[o];
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u) xv[u] = x[(int64_t)j[u] * stride];
+#pragma unroll
+    for (int u = 0; u < CH; ++u)
+      if (t0 + u < R.len) acc = acc + v[u] * xv[u];
+  }
+  return acc;
+}
+
 // The same sum over a SELL of uniform slice width A.uw: the row's entries sit
 // at addresses known from r alone, so they load with x's first gathers' index
 // loads and without the row length.  Slots past the row's end hold column 0

@@ -922,71 +922,6 @@ __global__ void __launch_bounds__(kBlock) k_coarse_inverse_lds(const double* __r
   for (int32_t i = threadIdx.x; i < ld; i += kBlock) inv[(int64_t)c * ld + i] = i < n ? col[i] : 0.0;
 }
 
-// Longest row of every colour, rounded up to kTailGroup: w[c].
-__global__ void k_color_width(const int32_t* len, const int32_t* cptr, int32_t* w) {
-  __shared__ int32_t ws[kBlock / kWave];
-  const int c = blockIdx.x;
-  int32_t m = 0;
-  for (int32_t r = cptr[c] + threadIdx.x; r < cptr[c + 1]; r += kBlock) m = len[r] > m ? len[r] : m;
-  for (int o = 32; o > 0; o >>= 1) {
-    const int32_t t = __shfl_xor(m, o, kWave);
-    m = t > m ? t : m;
-  }
-  if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < kBlock / kWave; ++i) m = ws[i] > m ? ws[i] : m;
-    w[c] = (m + kTailGroup - 1) / kTailGroup * kTailGroup;
-  }
-}
-
-// A_l (SELL) into the tail's per-colour ELL, with and without the diagonal,
-// and every row's wavefront width: the longest row of its 64-row chunk of the
-// colour, rounded up to 4 entries.
-__global__ void k_tail_ell(SellView A, const int32_t* cinfo, int nc, int64_t n, int32_t* col_gs, double* val_gs,
-                           int32_t* col, double* val, uint16_t* ww) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  int c = 0;
-  while (c + 1 < nc && cinfo[4 * (c + 1)] <= r) ++c;
-  const int32_t lo = cinfo[4 * c], hi = cinfo[4 * c + 1], w = cinfo[4 * c + 2], off = cinfo[4 * c + 3];
-  const int32_t len = A.len[r];
-  {
-    const int32_t c0 = lo + (int32_t)((r - lo) & ~(int64_t)(kWave - 1));
-    const int32_t c1 = min(c0 + kWave, hi);
-    int32_t m = 0;
-    for (int32_t q = c0; q < c1; ++q) m = max(m, A.len[q]);
-    ww[r] = (uint16_t)min((m + 3) & ~3, w);
-  }
-  const int64_t base = A.ptr[r / kSlice] + (r & (kSlice - 1));
-  for (int32_t t = 0; t < w; ++t) {
-    const int64_t oc = ell_col_index(off, hi - lo, lo, r, t), ov = ell_val_index(off, hi - lo, lo, r, t);
-    int32_t j = (int32_t)n;
-    double v = 0.0;
-    if (t < len) {
-      j = A.col[base + (int64_t)t * kSlice];
-      v = A.val[base + (int64_t)t * kSlice];
-    }
-    col[oc] = j;
-    val[ov] = v;
-    col_gs[oc] = j == r ? (int32_t)n : j;
-    val_gs[ov] = j == r ? 0.0 : v;
-  }
-}
-
-// P_l^T (SELL, nc rows) into ELL of width w; padding column n (the fine level's size).
-__global__ void k_tail_ell_t(SellView T, int64_t nc, int32_t w, int64_t n, int32_t* col, double* val) {
-  const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t len = T.len[I];
-  const int64_t base = T.ptr[I / kSlice] + (I & (kSlice - 1));
-  for (int32_t t = 0; t < w; ++t) {
-    col[ell_col_index(0, nc, 0, I, t)] = t < len ? T.col[base + (int64_t)t * kSlice] : (int32_t)n;
-    val[ell_val_index(0, nc, 0, I, t)] = t < len ? T.val[base + (int64_t)t * kSlice] : 0.0;
-  }
-}
-
-
 // ------------------------------------------------------------------ block order
 // Order-preserving 64-bit key of a double (a larger double gets a larger
 // key), so that minima and maxima are exact integer atomics.
@@ -2175,65 +2110,23 @@ void refresh_values(Handle& h, Level& lv) {
                                                          (int32_t*)v.A.col, (double*)v.A.val, lv.diag);
 }
 
-// The levels of the single-workgroup tail keep blocked ELL copies of A_l and
-// P_l^T.  (The same layout for the multi-launch Gauss-Seidel kernels of the
-// Galerkin levels measured no faster than SELL: their launches are bound by
-// the per-launch cost.)
-int ell_first_level(const Handle& h) { return h.tail_start; }
-
-// Blocked ELL copies of A_l and P_l^T (see LevelViewT): colour widths are read
-// back once to lay the colours out.
-void ell_layout(Handle& h, Level& lv, const Level& nx) {
-  hipStream_t s = h.stream;
-  LevelView& v = lv.view;
-  const int C = v.ncolors;
-  int32_t* w = (int32_t*)talloc(s, (size_t)C * 4);
-  k_color_width<<<C, kBlock, 0, s>>>(v.A.len, v.cptr, w);
-  int32_t* stage = (int32_t*)pinned_staging((size_t)C * 4);
-  check_hip(hipMemcpyAsync(stage, w, (size_t)C * 4, hipMemcpyDeviceToHost, s), "copy");
-  sync(s, "tail layout");
-  tfree(s, w);
-  lv.e_cinfo_h.assign((size_t)4 * C, 0);
-  int64_t off = 0;
-  for (int c = 0; c < C; ++c) {
-    const int32_t lo = lv.color_ptr[c], hi = lv.color_ptr[c + 1];
-    lv.e_cinfo_h[4 * c] = lo;
-    lv.e_cinfo_h[4 * c + 1] = hi;
-    lv.e_cinfo_h[4 * c + 2] = stage[c];
-    lv.e_cinfo_h[4 * c + 3] = (int32_t)off;
-    off += (int64_t)stage[c] * (hi - lo);
-  }
-  lv.e_slots = off;
-  v.e_slots = (int32_t)off;
-  int32_t* cinfo = (int32_t*)dalloc(h, (size_t)4 * C * 4);
-  int32_t* st = (int32_t*)pinned_staging((size_t)4 * C * 4);
-  std::copy(lv.e_cinfo_h.begin(), lv.e_cinfo_h.end(), st);
-  check_hip(hipMemcpyAsync(cinfo, st, (size_t)4 * C * 4, hipMemcpyHostToDevice, s), "copy");
-  v.e_cinfo = cinfo;
-  const size_t e = (size_t)std::max<int64_t>(off, 1);
-  v.e_col_gs = (int32_t*)dalloc(h, e * 4);
-  v.e_col = (int32_t*)dalloc(h, e * 4);
-  v.e_val_gs = (double*)dalloc(h, e * 8);
-  v.e_val = (double*)dalloc(h, e * 8);
-  v.e_ww = (uint16_t*)dalloc(h, (size_t)lv.n * 2);
-  ell_values(h, lv);
-  v.e_wt = (v.maxt + kTailGroup - 1) / kTailGroup * kTailGroup;
-  lv.e_tslots = (int64_t)v.e_wt * nx.n;
-  v.e_tslots = (int32_t)lv.e_tslots;
-  const size_t et = (size_t)std::max<int64_t>(lv.e_tslots, 1);
-  int32_t* tcol = (int32_t*)dalloc(h, et * 4);
-  double* tval = (double*)dalloc(h, et * 8);
-  k_tail_ell_t<<<blocks_for(nx.n), kBlock, 0, s>>>(v.T, nx.n, v.e_wt, lv.n, tcol, tval);
-  v.e_tcol = tcol;
-  v.e_tval = tval;
-  sync(s, "tail layout");   // the staging buffer is reused by the next call
-}
-
-void ell_values(Handle& h, Level& lv) {
+template <class V>
+void tail_layout(Handle& h, const Level& lv, TailRows<V>& R) {
   const LevelView& v = lv.view;
-  k_tail_ell<<<blocks_for(lv.n), kBlock, 0, h.stream>>>(v.A, v.e_cinfo, v.ncolors, lv.n, (int32_t*)v.e_col_gs,
-                                                        (double*)v.e_val_gs, (int32_t*)v.e_col, (double*)v.e_val,
-                                                        (uint16_t*)v.e_ww);
+  if (!R.col) {
+    const int32_t W = tail_width(v.maxa);
+    R.nchunk = 0;
+    for (size_t c = 0; c + 1 < lv.color_ptr.size(); ++c)
+      R.nchunk += (lv.color_ptr[c + 1] - lv.color_ptr[c] + kWave - 1) / kWave;
+    const size_t e = (size_t)R.nchunk * kWave * W;
+    R.chunk = (int4*)dalloc(h, (size_t)R.nchunk * sizeof(int4));
+    R.info = (int32_t*)dalloc(h, (size_t)lv.n * 4);
+    R.col = (uint16_t*)dalloc(h, e * 2);
+    R.val = (V*)dalloc(h, e * sizeof(V));
+  }
+  tail_fill<V>(v, R.nchunk, (int4*)R.chunk, (int32_t*)R.info, (uint16_t*)R.col, (V*)R.val, h.stream);
 }
+template void tail_layout<double>(Handle&, const Level&, TailRows<double>&);
+template void tail_layout<float>(Handle&, const Level&, TailRows<float>&);
 
 }  // namespace gmg

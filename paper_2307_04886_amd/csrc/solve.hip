@@ -1,9 +1,9 @@
 // V-cycle kernels (Alg. 2): multicolour Gauss-Seidel, residual, restriction
-// by P^T, prolongation and correction, coarsest-level solve, norms.
+// by P^T, prolongation and correction, norms.
 //
 // Every kernel is written once for the value type V of the level data: double
 // for the solve of Alg. 1, float for the mixed-precision CG preconditioner.
-// The coarsest level is always solved in double with the dense inverse.
+// The levels with few rows and the coarsest solve are in tail.hip.
 #include <type_traits>
 
 #include "rows.hpp"
@@ -302,422 +302,6 @@ __global__ void __launch_bounds__(kBlock) k_prolong_correct(LevelViewT<V> L, con
   prolong_row(L, xc, x, (int32_t)i);
 }
 
-// x = A_c^-1 b in double (b widened from V, x rounded to V): row i is the sum
-// over k ascending of (A_c^-1 e_k)_i b_k, stored at inv[k ld + i]; one thread
-// per row (the loads of a wavefront are coalesced).
-template <class V>
-__global__ void __launch_bounds__(kBlock) k_dense_gemv(const double* __restrict__ M, const V* __restrict__ b,
-                                                       V* __restrict__ x, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  double acc = 0.0;
-  const int64_t ld = inv_ld(n);
-  // the loads of eight terms are issued before they are added (in ascending k)
-  int64_t k = 0;
-  for (; k + 8 <= n; k += 8) {
-    double m[8], v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      m[u] = M[(k + u) * ld + i];
-      v[u] = (double)b[k + u];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc = acc + m[u] * v[u];
-  }
-  for (; k < n; ++k) acc = acc + M[k * ld + i] * (double)b[k];
-  x[i] = (V)acc;
-}
-
-// The V-cycle below a level with few rows, in one workgroup: every phase
-// (colour of a sweep, residual, restriction, coarsest solve, prolongation) is
-// separated by a workgroup barrier instead of a kernel boundary, and the tail
-// levels' vectors x, b and r live in LDS.  Each phase performs exactly the
-// operations of the corresponding multi-launch kernel, in the same order.
-//
-// One lane per row, four wavefronts (one per SIMD, so that a lane can hold a
-// whole row in registers).  Rows are handled in rounds of kTailThreads1 rows;
-// the matrix entries of the next round, which do not depend on x, are loaded
-// before the current round computes, so that their latency overlaps the
-// current round and the barrier that ends a colour.  The matrices are read in
-// the per-colour ELL of the tail levels (see LevelViewT), whose padded terms
-// are exactly +0.
-constexpr int kTailThreads1 = 256;
-constexpr int kTailW = 32;                 // entries of a row held in registers; the rest load on demand
-constexpr int kTailProlong = 4;            // prolongation rows per thread whose loads are issued together
-constexpr int kTailGemv = 16;              // columns of the coarsest inverse per prefetched chunk
-constexpr int kTailLoad = 16;              // elements per thread of the first tail level's loads into LDS
-
-struct TailSeg {
-  int32_t lo, hi, w, off;                  // rows [lo, hi), ELL width, offset of entry (0, lo)
-};
-
-template <class V>
-struct TailRow {
-  int32_t j[kTailW];
-  V v[kTailW];
-  V d;
-  int32_t w;                               // entries loaded for the wavefront's rows (uniform)
-};
-
-__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Tail matrix loads go through buffer resources: a scalar base and bound, a
-// uniform (scalar) offset for the entry column and the lane's row offset, so
-// that no vector instruction is spent on addresses.
-using Rsrc = __amdgpu_buffer_rsrc_t;
-__device__ __forceinline__ Rsrc make_rsrc(const void* p, int64_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(uint32_t)bytes, 0x00020000);
-}
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x4 bload16(Rsrc r, uint32_t voff, uint32_t soff) {
-  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-}
-// (the 8-byte form returns one 64-bit integer)
-__device__ __forceinline__ uint64_t bload8(Rsrc r, uint32_t voff, uint32_t soff) {
-  return (uint64_t)__builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
-}
-__device__ __forceinline__ double as_f64(uint32_t lo, uint32_t hi) {
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// Two consecutive values of a tail ELL value array (one block) for one lane.
-template <class V>
-__device__ __forceinline__ void val_pair(Rsrc r, uint32_t voff, uint32_t soff, V& a, V& b);
-template <>
-__device__ __forceinline__ void val_pair<double>(Rsrc r, uint32_t voff, uint32_t soff, double& a, double& b) {
-  const u32x4 u = bload16(r, voff * 16u, soff * 8u);
-  a = as_f64(u.x, u.y);
-  b = as_f64(u.z, u.w);
-}
-template <>
-__device__ __forceinline__ void val_pair<float>(Rsrc r, uint32_t voff, uint32_t soff, float& a, float& b) {
-  const uint64_t u = bload8(r, voff * 8u, soff * 4u);
-  a = __builtin_bit_cast(float, (uint32_t)u);
-  b = __builtin_bit_cast(float, (uint32_t)(u >> 32));
-}
-
-// An ELL matrix of the tail: column and value arrays.
-template <class V>
-struct TailMat {
-  Rsrc col, val;
-};
-template <class V>
-__device__ __forceinline__ TailMat<V> tail_mat(const int32_t* col, const V* val, int64_t slots) {
-  return TailMat<V>{make_rsrc(col, slots * 4), make_rsrc(val, slots * (int64_t)sizeof(V))};
-}
-
-// Entries t0..t0+3 of the lane's row (row offset lo in a segment of cnt rows
-// at element offset off): one 4-entry column block, two 2-entry value blocks.
-template <class V>
-__device__ __forceinline__ void tail_quad(const TailMat<V>& M, uint32_t off, uint32_t cnt, uint32_t lo,
-                                          uint32_t t0, int32_t* j, V* v) {
-  const u32x4 c = bload16(M.col, lo * 16u, (off + (t0 >> 2) * cnt * 4u) * 4u);
-  j[0] = (int32_t)c.x;
-  j[1] = (int32_t)c.y;
-  j[2] = (int32_t)c.z;
-  j[3] = (int32_t)c.w;
-#pragma unroll
-  for (int b = 0; b < 2; ++b) val_pair<V>(M.val, lo, off + ((t0 >> 1) + b) * cnt * 2u, v[2 * b], v[2 * b + 1]);
-}
-
-// A row offset whose lane offsets (16 or 8 bytes per row) lie past every tail
-// array: such a buffer load reads no memory and returns zeros.
-constexpr uint32_t kTailNoRow = 0x08000000u;
-
-// Entries 0..kTailW-1 of row r (clamped into the segment by the caller), up to
-// w (uniform over the wavefront, a multiple of 4 within the segment's width),
-// and its diagonal when D.  The quads past w are loads out of the buffer's
-// range (no memory traffic), so that every round issues the same number of
-// loads and the consumer of a round waits only for that round's loads, not
-// for the next round's already in flight.
-template <bool D, class V>
-__device__ __forceinline__ void tail_fetch(const TailMat<V>& M, const V* diag, const TailSeg& sg, int32_t r,
-                                           int32_t w, TailRow<V>& q) {
-  const uint32_t cnt = (uint32_t)(sg.hi - sg.lo);
-  const uint32_t lo = (uint32_t)(r - sg.lo);
-  q.w = w;
-#pragma unroll
-  for (int g = 0; g < kTailW / 4; ++g)
-    tail_quad(M, (uint32_t)sg.off, cnt, 4 * g < w ? lo : kTailNoRow, (uint32_t)(4 * g), q.j + 4 * g, q.v + 4 * g);
-  if (D) q.d = diag[r];
-}
-
-// sum over the row's entries in entry order of val * X[col]; the entries past
-// the row's end up to the wavefront's width are padding (+0 terms)
-template <class V>
-__device__ __forceinline__ V tail_sum(const TailMat<V>& M, const TailSeg& sg, int32_t r, const TailRow<V>& q,
-                                      const V* X) {
-  const int32_t w = q.w;
-  // all gathers first, so that they are in flight together
-  V xv[kTailW];
-#pragma unroll
-  for (int g = 0; g < kTailW / 4; ++g)
-    if (4 * g < w) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) xv[4 * g + u] = X[q.j[4 * g + u]];
-    }
-  V acc = V(0);
-#pragma unroll
-  for (int g = 0; g < kTailW / 4; ++g)
-    if (4 * g < w) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc = acc + q.v[4 * g + u] * xv[4 * g + u];
-    }
-  const uint32_t cnt = (uint32_t)(sg.hi - sg.lo);
-  const uint32_t lo = (uint32_t)(r - sg.lo);
-  for (int32_t t0 = kTailW; t0 < w; t0 += 4) {
-    int32_t j[4];
-    V v[4];
-    tail_quad(M, (uint32_t)sg.off, cnt, lo, (uint32_t)t0, j, v);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc = acc + v[u] * X[j[u]];
-  }
-  return acc;
-}
-
-// Runs the rows of segments 0..nseg-1 (seg(s) -> TailSeg) through the
-// pipeline; out(r, acc, diag) consumes each row's sum.  A wavefront loads the
-// entries up to WW[r] of its rows (WW in LDS, the same for the wavefront's 64
-// rows), or up to the segment's width when WW is null.  A workgroup barrier
-// follows every segment when `barrier_each` (colours of a sweep), else only
-// the last.  Two row buffers alternate (no copies between rounds).
-template <bool D, class V, class Seg, class Out>
-__device__ __forceinline__ void tail_rows(const TailMat<V>& M, const V* diag, const uint16_t* WW, int nseg, Seg seg,
-                                          const V* X, bool barrier_each, Out out) {
-  const int32_t tid = threadIdx.x;
-  auto width = [&](const TailSeg& g, int32_t r) { return WW ? uniform((int32_t)WW[r]) : g.w; };
-  TailSeg sg = seg(0);
-  int s = 0;
-  int32_t r0 = sg.lo;
-  TailRow<V> ra, rb;
-  {
-    const int32_t r = max(min(r0 + tid, sg.hi - 1), 0);
-    tail_fetch<D>(M, diag, sg, r, width(sg, r), ra);
-  }
-  // one round: loads the next round into nxt, then computes cur; false after the last
-  auto round = [&](TailRow<V>& cur, TailRow<V>& nxt) {
-    TailSeg sg2 = sg;
-    int s2 = s;
-    int32_t r2 = r0 + kTailThreads1;
-    const bool last_round = r2 >= sg.hi;
-    if (last_round) {
-      s2 = s + 1;
-      if (s2 < nseg) {
-        sg2 = seg(s2);
-        r2 = sg2.lo;
-      }
-    }
-    const bool more = s2 < nseg;
-    if (!more) {                // the loads stay unconditional (same count in flight on every path)
-      sg2 = sg;
-      r2 = r0;
-    }
-    {
-      const int32_t rn = max(min(r2 + tid, sg2.hi - 1), 0);
-      tail_fetch<D>(M, diag, sg2, rn, width(sg2, rn), nxt);
-    }
-    const int32_t r = r0 + tid;
-    const V acc = tail_sum(M, sg, max(min(r, sg.hi - 1), 0), cur, X);
-    if (r < sg.hi) out(r, acc, cur.d);
-    if (last_round && (barrier_each || !more)) __syncthreads();
-    sg = sg2;
-    s = s2;
-    r0 = r2;
-    return more;
-  };
-  while (round(ra, rb) && round(rb, ra)) {
-  }
-}
-
-template <class V>
-struct TailLds {
-  V *x, *b, *r;
-  const int4* c;                           // colour table (lo, hi, w, off)
-  const uint16_t* w;                       // rows' wavefront widths
-};
-
-template <class V>
-__device__ __forceinline__ TailLds<V> tail_lds(const TailDescT<V>& d, char* lds, int l) {
-  TailLds<V> t;
-  t.x = reinterpret_cast<V*>(lds + d.o_x[l]);
-  t.b = reinterpret_cast<V*>(lds + d.o_b[l]);
-  t.r = reinterpret_cast<V*>(lds + d.o_r[l]);
-  t.c = reinterpret_cast<const int4*>(lds + d.o_c[l]);
-  t.w = reinterpret_cast<const uint16_t*>(lds + d.o_w[l]);
-  return t;
-}
-
-__device__ __forceinline__ TailSeg colour_seg(const int4* ct, int c) {
-  const int4 e = ct[c];
-  return TailSeg{uniform(e.x), uniform(e.y), uniform(e.z), uniform(e.w)};
-}
-
-// nsweeps Gauss-Seidel sweeps over the colours of one tail level.
-template <class V>
-__device__ __forceinline__ void tail_gs(const LevelViewT<V>& L, const TailLds<V>& t, int nsweeps, bool descending) {
-  const int nc = L.ncolors;
-  if (nsweeps <= 0) return;
-  tail_rows<true>(
-      tail_mat(L.e_col_gs, L.e_val_gs, L.e_slots), L.diag, t.w, nsweeps * nc,
-      [&](int s) {
-        const int i = s % nc;
-        return colour_seg(t.c, descending ? nc - 1 - i : i);
-      },
-      t.x, true, [&](int32_t r, V acc, V dr) { t.x[r] = (t.b[r] - acc) / dr; });
-}
-
-template <class V>
-__global__ void __launch_bounds__(kTailThreads1) k_tail_vcycle(TailDescT<V> d) {
-  extern __shared__ double lds_raw[];
-  char* lds = reinterpret_cast<char*>(lds_raw);
-  const int tid = threadIdx.x;
-  const int lc = d.nlev - 1;   // the coarsest level
-  // the first tail level's x and b (and, when it is not the coarsest, its
-  // rows' widths) with its colour table: each chunk's loads are all issued
-  // before its LDS writes, so that they wait on one memory latency
-  {
-    const LevelViewT<V>& L = d.lv[0];
-    const TailLds<V> t = tail_lds(d, lds, 0);
-    const int32_t n = L.n;
-    const bool smoothed = lc > 0;
-    uint16_t* ww = reinterpret_cast<uint16_t*>(lds + d.o_w[0]);
-    for (int32_t i0 = 0; i0 < n; i0 += kTailLoad * kTailThreads1) {
-      V xv[kTailLoad], bv[kTailLoad];
-      uint16_t wv[kTailLoad];
-#pragma unroll
-      for (int u = 0; u < kTailLoad; ++u) {
-        const int32_t i = min(i0 + u * kTailThreads1 + tid, n - 1);
-        xv[u] = L.x[i];
-        bv[u] = L.b[i];
-        wv[u] = smoothed ? L.e_ww[i] : (uint16_t)0;
-      }
-      if (i0 == 0 && smoothed) {
-        int32_t* ct = reinterpret_cast<int32_t*>(lds + d.o_c[0]);
-        for (int i = tid; i < 4 * L.ncolors; i += kTailThreads1) ct[i] = L.e_cinfo[i];
-      }
-#pragma unroll
-      for (int u = 0; u < kTailLoad; ++u) {
-        const int32_t i = i0 + u * kTailThreads1 + tid;
-        if (i < n) {
-          t.x[i] = xv[u];
-          t.b[i] = bv[u];
-          if (smoothed) ww[i] = wv[u];
-        }
-      }
-    }
-  }
-  // the other smoothed tail levels' colour tables and widths; the zeros behind x and r
-  for (int l = 0; l < lc; ++l) {
-    const LevelViewT<V>& L = d.lv[l];
-    const TailLds<V> t = tail_lds(d, lds, l);
-    if (l > 0) {
-      int32_t* ct = reinterpret_cast<int32_t*>(lds + d.o_c[l]);
-      for (int i = tid; i < 4 * L.ncolors; i += kTailThreads1) ct[i] = L.e_cinfo[i];
-      uint16_t* ww = reinterpret_cast<uint16_t*>(lds + d.o_w[l]);
-      for (int i = tid; i < L.n; i += kTailThreads1) ww[i] = L.e_ww[i];
-    }
-    if (tid == 0) {
-      t.x[L.n] = V(0);
-      t.r[L.n] = V(0);
-    }
-  }
-  __syncthreads();
-  for (int l = 0; l < lc; ++l) {
-    const LevelViewT<V>& L = d.lv[l];
-    const TailLds<V> t = tail_lds(d, lds, l);
-    tail_gs(L, t, d.nu_pre, false);
-    // r = b - A x, colour by colour
-    tail_rows<false>(
-        tail_mat(L.e_col, L.e_val, L.e_slots), L.diag, t.w, L.ncolors, [&](int s) { return colour_seg(t.c, s); },
-        t.x, false,
-        [&](int32_t r, V acc, V) { t.r[r] = t.b[r] - acc; });
-    // b_c = P^T r, x_c = 0
-    const TailLds<V> tc = tail_lds(d, lds, l + 1);
-    const int32_t nc = d.lv[l + 1].n;
-    tail_rows<false>(
-        tail_mat(L.e_tcol, L.e_tval, L.e_tslots), L.diag, nullptr, 1,
-        [&](int) { return TailSeg{0, nc, uniform(L.e_wt), 0}; },
-        t.r, false,
-        [&](int32_t r, V acc, V) {
-          tc.b[r] = acc;
-          tc.x[r] = V(0);
-        });
-  }
-  {
-    // x_c = A_c^-1 b_c in double: row i is the sum over k ascending of
-    // (A_c^-1 e_k)_i b_k, stored at inv[k ld + i].  Each lane sums two rows
-    // (2l, 2l + 1: one 16-byte load per column); the next chunk of columns is
-    // loaded while one is summed.
-    const TailLds<V> t = tail_lds(d, lds, lc);
-    const int32_t n = d.lv[lc].n;
-    const int32_t ld = (int32_t)inv_ld(n);
-    const Rsrc inv = make_rsrc(d.cinv, (int64_t)n * ld * 8);
-    for (int32_t i0 = 0; i0 < n; i0 += 2 * kTailThreads1) {
-      const int32_t i = min(i0 + 2 * tid, ld - 2);       // even: rows i, i + 1 (i + 1 = ld - 1 may be padding)
-      u32x4 m[kTailGemv], mn[kTailGemv];
-#pragma unroll
-      for (int u = 0; u < kTailGemv; ++u) m[u] = bload16(inv, (uint32_t)i * 8u, (uint32_t)(min(u, n - 1) * ld) * 8u);
-      double acc0 = 0.0, acc1 = 0.0;
-      for (int32_t k0 = 0; k0 < n; k0 += kTailGemv) {
-#pragma unroll
-        for (int u = 0; u < kTailGemv; ++u)
-          mn[u] = bload16(inv, (uint32_t)i * 8u, (uint32_t)(min(k0 + kTailGemv + u, n - 1) * ld) * 8u);
-#pragma unroll
-        for (int u = 0; u < kTailGemv; ++u)
-          if (k0 + u < n) {
-            const double bk = (double)t.b[min(k0 + u, n - 1)];
-            acc0 = acc0 + as_f64(m[u].x, m[u].y) * bk;
-            acc1 = acc1 + as_f64(m[u].z, m[u].w) * bk;
-          }
-#pragma unroll
-        for (int u = 0; u < kTailGemv; ++u) m[u] = mn[u];
-      }
-      const int32_t r = i0 + 2 * tid;
-      if (r < n) t.x[r] = (V)acc0;
-      if (r + 1 < n) t.x[r + 1] = (V)acc1;
-    }
-    __syncthreads();
-  }
-  for (int l = lc - 1; l >= 0; --l) {
-    const LevelViewT<V>& L = d.lv[l];
-    const TailLds<V> t = tail_lds(d, lds, l);
-    const V* XC = tail_lds(d, lds, l + 1).x;
-    // x_i += sum_t P[i, t] x_c[col_t]; the loads of kTailProlong rows per thread are issued together
-    for (int32_t i0 = 0; i0 < L.n; i0 += kTailProlong * kTailThreads1) {
-      int32_t c[kTailProlong];
-      int32_t j[kTailProlong][3];
-      V v[kTailProlong][3];
-#pragma unroll
-      for (int u = 0; u < kTailProlong; ++u) {
-        const int32_t i = min(i0 + u * kTailThreads1 + tid, L.n - 1);
-        c[u] = L.q_cnt[i];
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-          j[u][e] = L.q_col[(int64_t)e * L.n + i];
-          v[u][e] = L.q_val[(int64_t)e * L.n + i];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kTailProlong; ++u) {
-        const int32_t i = i0 + u * kTailThreads1 + tid;
-        if (i < L.n) {
-          V acc = V(0);
-#pragma unroll
-          for (int e = 0; e < 3; ++e)
-            if (e < c[u]) acc = acc + v[u][e] * XC[j[u][e]];
-          t.x[i] = t.x[i] + acc;
-        }
-      }
-    }
-    __syncthreads();
-    tail_gs(L, t, d.nu_post, d.descending_post != 0);
-  }
-  {
-    const TailLds<V> t = tail_lds(d, lds, 0);
-    for (int32_t i = tid; i < d.lv[0].n; i += kTailThreads1) d.lv[0].x[i] = t.x[i];
-  }
-}
-
 __global__ void k_gather(const int32_t* perm, const double* src, double* dst, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = src[perm[i]];
@@ -872,16 +456,6 @@ void prolong_correct(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t
 }
 
 template <class V>
-void coarse_solve(const double* cinv, const LevelViewT<V>& c, hipStream_t s) {
-  k_dense_gemv<V><<<blocks_for(c.n), kBlock, 0, s>>>(cinv, c.b, c.x, c.n);
-}
-
-template <class V>
-void tail_vcycle(const TailDescT<V>& d, hipStream_t s) {
-  k_tail_vcycle<V><<<1, kTailThreads1, (size_t)d.lds_bytes, s>>>(d);
-}
-
-template <class V>
 void fill_zero(V* p, int64_t n, hipStream_t s) {
   k_zero<V><<<blocks_for(n), kBlock, 0, s>>>(p, n);
 }
@@ -927,8 +501,6 @@ void check_finite(const double* v, int64_t n, int32_t* flag, hipStream_t s) {
   template void residual<V>(const LevelViewT<V>&, hipStream_t, bool);                                  \
   template void restrict_to<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t, int32_t);      \
   template void prolong_correct<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);           \
-  template void coarse_solve<V>(const double*, const LevelViewT<V>&, hipStream_t);                     \
-  template void tail_vcycle<V>(const TailDescT<V>&, hipStream_t);                                      \
   template void fill_zero<V>(V*, int64_t, hipStream_t);                                                \
   template void permute_out<V>(const int32_t*, const V*, double*, int64_t, hipStream_t);
 GMG_INSTANTIATE(double)

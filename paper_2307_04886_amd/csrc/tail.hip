@@ -1,0 +1,658 @@
+// The V-cycle on levels with few rows (Alg. 2): all Gauss-Seidel sweeps of one
+// level, the residual after them or the correction before them, in one
+// workgroup; and the restriction into the coarsest level fused with its direct
+// solve.  Grids of these kernels run one workgroup (or row of workgroups) per
+// vector: one for the solve, kBatch for the batched forms, whose vectors are
+// interleaved (entry (i, q) at i * stride + q).
+#include <algorithm>
+
+#include "rows.hpp"
+
+namespace gmg {
+
+namespace {
+
+// One colour of such a level has 100-300 rows, so a kernel per colour is all
+// launch latency (3 us against 0.3 us for its arithmetic), and the sweeps run
+// in one workgroup with a barrier per colour.  A phase (colour) is a few
+// wavefronts' worth of rows, each a chain of dependent operations on a nearly
+// empty compute unit, so its time is the number of instructions a wavefront
+// issues, and the latency of every load that was not issued phases ahead:
+//  - each colour's rows (consecutive in the solve numbering) are cut into
+//    chunks of one wavefront; chunk q belongs to wavefront q mod 8, which holds
+//    its rows' entries in registers (up to W a row, the column a 16-bit byte
+//    offset into the iterate in LDS), a row per lane.  A wavefront's control
+//    flow is then its list of chunks: wait for the chunk's phase, sum, write;
+//  - levels of at most 8 NB chunks are loaded once per call and stay; larger
+//    ones reload a buffer as soon as its rows are done, NB chunks of the
+//    wavefront (two to five phases each) ahead of their use;
+//  - a wavefront loads 16 bytes per lane and instruction, contiguous, and only
+//    as many entries as its chunk's longest row.
+// Rows sum their terms in entry order; the diagonal entry points at a zero
+// kept behind x in the sweeps (its product is +0, which leaves the sum
+// unchanged: a sum that starts at +0 is never -0) and at the row itself in the
+// residual.
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The row buffers load through buffer resources: a scalar base and bound, the
+// thread's offset in one register and a uniform offset for the block of
+// entries, so that no registers go to addresses.
+using Rsrc = __amdgpu_buffer_rsrc_t;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Rsrc make_rsrc(const void* p, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(uint32_t)bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 bload16(Rsrc r, uint32_t voff, uint32_t soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
+}
+
+// A chunk's rows, one per lane: the loaded 16-byte blocks as they came (eight
+// 16-bit column offsets, E values).
+template <class V, int W>
+struct TailBuf {
+  static constexpr int E = 16 / sizeof(V);
+  u32x4 c[W / 8];
+  u32x4 v[W / E];
+  V b, d;
+  int32_t info;                            // row length << 8 | entry of the diagonal
+  int4 q;                                  // first row, rows, colour, entries of the longest row (all uniform)
+  __device__ __forceinline__ V value(int t) const {
+    const u32x4 a = v[t / E];
+    if constexpr (sizeof(V) == 8) {
+      return __builtin_bit_cast(V, (uint64_t)a[2 * (t % E) + 1] << 32 | a[2 * (t % E)]);
+    } else {
+      const uint32_t u = a[t % E];         // a value of its own: bit_cast of a vector's element takes the first
+      return __builtin_bit_cast(V, u);
+    }
+  }
+};
+
+// Chunk `chunk`, whose entry of the chunk table is q.
+template <class V, int W>
+__device__ __forceinline__ void tail_load(const TailJob<V>& J, const V* b, int32_t chunk, int4 q, TailBuf<V, W>& f) {
+  constexpr int E = TailBuf<V, W>::E;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  f.q = int4{uniform(q.x), uniform(q.y), uniform(q.z), uniform(q.w)};
+  const int32_t r = f.q.x + min((int32_t)lane, f.q.y - 1);
+  f.b = b[(int64_t)r * J.stride];
+  f.d = J.diag[r];
+  f.info = J.A.info[r];
+  constexpr uint32_t kC = W * 2 * kWave, kV = W * sizeof(V) * kWave;    // bytes of a chunk
+  const Rsrc cr = make_rsrc(J.A.col, (int64_t)J.A.nchunk * kC), vr = make_rsrc(J.A.val, (int64_t)J.A.nchunk * kV);
+#pragma unroll
+  for (int g = 0; g < W / 8; ++g) {
+    if (g == 0 || 8 * g < f.q.w) {
+      f.c[g] = bload16(cr, lane * 16u, (uint32_t)chunk * kC + g * (kWave * 16u));
+#pragma unroll
+      for (int u = 0; u < 8 / E; ++u)
+        f.v[8 / E * g + u] = bload16(vr, lane * 16u, (uint32_t)chunk * kV + (8 / E * g + u) * (kWave * 16u));
+    }
+  }
+}
+
+// The iterate's element at byte offset o: it starts the dynamic LDS, at LDS
+// address 0 since these kernels have no other (an address of its own would cost
+// an addition per gather).
+template <class V>
+__device__ __forceinline__ V lds_at(uint32_t o) {
+  return *(const __attribute__((address_space(3))) V*)o;
+}
+
+// sum of the row's terms in entry order; Res: the diagonal's included.  The
+// gathers of kTailGather entries are in flight together.
+constexpr int kTailGather = 16;
+template <bool Res, class V, int W>
+__device__ __forceinline__ V tail_sum(const TailJob<V>& J, const TailBuf<V, W>& f, int32_t row) {
+  constexpr int G = W < kTailGather ? W : kTailGather;
+  // the width and the columns are kept as they are: without this the compiler
+  // computes every resident row's conditions and addresses once, outside the
+  // sweeps, and spills them
+  int32_t w = uniform(f.q.w);
+  asm volatile("" : "+s"(w));
+  const int32_t dp = f.info & 0xFF;
+  V s = V(0);
+#pragma unroll
+  for (int g0 = 0; g0 < W; g0 += G) {
+    if (g0 == 0 || g0 < w) {
+      V xv[G];
+#pragma unroll
+      for (int h = 0; h < G; h += 8)
+        if (g0 + h == 0 || g0 + h < w) {
+          u32x4 c = f.c[(g0 + h) / 8];
+          asm volatile("" : "+v"(c));
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            uint32_t o = (u & 1) ? c[u / 2] >> 16 : c[u / 2] & 0xFFFFu;
+            if constexpr (Res) o = g0 + h + u == dp ? (uint32_t)row * (uint32_t)sizeof(V) : o;
+            xv[h + u] = lds_at<V>(o);
+          }
+        }
+#pragma unroll
+      for (int h = 0; h < G; h += 8)
+        if (g0 + h == 0 || g0 + h < w) {
+#pragma unroll
+          for (int u = 0; u < 8; ++u) s = s + f.value(g0 + h + u) * xv[h + u];
+        }
+    }
+  }
+  if constexpr (W == kTailWMax) {
+    // rows longer than the buffers: their further entries from the SELL copy
+    if (J.maxlen > W) {
+      const int32_t len = f.info >> 8;
+      const int64_t base = J.S.ptr[row / kSlice] + (row & (kSlice - 1));
+      for (int32_t t = W; t < len; ++t) {
+        const int32_t j = J.S.col[base + (int64_t)t * kSlice];
+        const V v = J.S.val[base + (int64_t)t * kSlice];
+        if (Res || j != row) s = s + v * lds_at<V>((uint32_t)j * (uint32_t)sizeof(V));
+      }
+    }
+  }
+  return s;
+}
+
+// LDS bytes of the iterate and its zero.
+template <class V>
+__host__ __device__ constexpr int32_t tail_lds(int32_t n) {
+  return (int32_t)(((n + 1) * sizeof(V) + 15) & ~(size_t)15);
+}
+
+// nsweeps sweeps over the level's colours (descending if J.descending), the
+// first J.skip colours of the first one already done; before them x += P x_c
+// when J.q_col is set, after them r = b - A x when J.r is set.  vec: the
+// vector's index in the interleaved arrays.  Phase p is colour p mod C of sweep
+// p / C; the residual follows the last phase.
+template <class V, int W, int NB, bool Stream>
+__device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
+  extern __shared__ double lds_raw[];
+  V* xl = reinterpret_cast<V*>(lds_raw);                      // [n + 1]
+  const int32_t t = threadIdx.x, lane = t & (kWave - 1), n = J.n, K = J.stride, C = J.ncolors;
+  constexpr int kWaves = kTailT / kWave;
+  const int32_t wv = uniform(t / kWave);
+  const V* b = J.b + vec;
+  V* x = J.x + vec;
+  const bool desc = J.descending != 0;
+  // this wavefront's chunks (wv, wv + 8, ..., or backwards from the last one
+  // of its own), visited in the same order in every pass
+  const int32_t mine = J.A.nchunk > wv ? (J.A.nchunk - wv + kWaves - 1) / kWaves : 0;
+  const int32_t passes = J.nsweeps + (J.r ? 1 : 0);
+  auto chunk_of = [&](int32_t k) { return wv + kWaves * (desc ? mine - 1 - k : k); };
+  // visit i starts in buffer i; streaming, visits may run over several passes
+  const int32_t visits = mine * passes;
+  auto starts = [&](int i) { return Stream ? i < visits : i < mine; };
+  auto start_chunk = [&](int i) { return chunk_of(Stream && i >= mine ? i % mine : i); };
+  int4 q0[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) q0[i] = J.A.chunk[starts(i) ? start_chunk(i) : 0];
+  if (t == 0) xl[n] = V(0);
+  // the iterate, corrected from the coarser level: its vector first into LDS
+  // (a gather of 64 cache lines takes the load path 64 cycles)
+  constexpr int Q = kTailRows / kTailT;    // one round
+  V* cl = reinterpret_cast<V*>(reinterpret_cast<char*>(lds_raw) + tail_lds<V>(n));    // [J.nc]; the chunk table follows in its place
+  if (J.q_col) {
+    const V* xc = J.xc + vec;
+    for (int32_t i = t; i < J.nc; i += kTailT) cl[i] = xc[(int64_t)i * K];
+  }
+  {
+    V xv[Q], p[Q][3];
+    int32_t cnt[Q], j[Q][3];
+#pragma unroll
+    for (int u = 0; u < Q; ++u) {
+      if (u * kTailT >= n) continue;
+      const int32_t i = min(u * kTailT + t, n - 1);
+      xv[u] = x[(int64_t)i * K];
+      if (J.q_col) {
+        cnt[u] = J.q_cnt[i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          j[u][a] = J.q_col[(int64_t)a * n + i];
+          p[u][a] = J.q_val[(int64_t)a * n + i];
+        }
+      }
+    }
+    if (J.q_col) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < Q; ++u) {
+        if (u * kTailT >= n) continue;
+        V acc = V(0);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+          if (a < cnt[u]) acc = acc + p[u][a] * cl[j[u][a]];
+        xv[u] = xv[u] + acc;
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < Q; ++u)
+      if (u * kTailT + t < n) xl[u * kTailT + t] = xv[u];
+  }
+  TailBuf<V, W> buf[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if (starts(i)) tail_load<V, W>(J, b, start_chunk(i), q0[i], buf[i]);
+  // the chunk table in LDS: a later load must not wait for memory to learn its width
+  int4* ct = reinterpret_cast<int4*>(reinterpret_cast<char*>(lds_raw) + tail_lds<V>(n));
+  if constexpr (Stream)
+    for (int32_t i = t; i < J.A.nchunk; i += kTailT) ct[i] = J.A.chunk[i];
+  __syncthreads();
+  // phases done by the whole workgroup (one barrier ends each)
+  int32_t phase = J.skip;
+  auto reach = [&](int32_t p) {
+    for (; phase < p; ++phase) __syncthreads();
+  };
+  // the phase of the chunk in f in the sweep whose first phase is p0
+  auto phase_of = [&](const TailBuf<V, W>& f, int32_t p0) {
+    const int32_t c = uniform(f.q.z);
+    return p0 + (desc ? C - 1 - c : c);
+  };
+  auto sweep_chunk = [&](const TailBuf<V, W>& f, int32_t p) {
+    if (p < J.skip) return;
+    reach(p);
+    if (lane < f.q.y) {
+      const int32_t row = f.q.x + lane;
+      xl[row] = (f.b - tail_sum<false>(J, f, row)) / f.d;
+    }
+  };
+  auto residual_chunk = [&](const TailBuf<V, W>& f) {
+    if (lane < f.q.y) {
+      const int32_t row = f.q.x + lane;
+      J.r[vec + (int64_t)row * K] = f.b - tail_sum<true>(J, f, row);
+    }
+  };
+  const int32_t end = J.nsweeps * C;
+  if constexpr (Stream) {
+    // k: place in the pass of the next visit; ahead: of the visit NB later
+    int32_t k = 0, p0 = 0, left = visits, ahead = mine > 0 ? NB % mine : 0;
+    while (left > 0) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (left > 0) {
+          if (p0 < end) {
+            const int32_t p = phase_of(buf[i], p0);
+            sweep_chunk(buf[i], p);
+            // end the phase before the reload when the wavefront's next chunk
+            // is in a later one: the others need not wait for its loads to issue
+            if (p >= J.skip && (left == 1 || k + 1 == mine || phase_of(buf[(i + 1) % NB], p0) > p)) reach(p + 1);
+          } else {
+            reach(end);
+            residual_chunk(buf[i]);
+          }
+          if (left > NB) tail_load<V, W>(J, b, chunk_of(ahead), ct[chunk_of(ahead)], buf[i]);
+          ahead = ahead + 1 == mine ? 0 : ahead + 1;
+          --left;
+          if (++k == mine) {
+            k = 0;
+            p0 += C;
+          }
+        }
+      }
+    }
+    reach(end);
+  } else {
+    for (int32_t p0 = 0; p0 < end; p0 += C) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (i < mine) sweep_chunk(buf[i], phase_of(buf[i], p0));
+    }
+    reach(end);
+    if (J.r) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (i < mine) residual_chunk(buf[i]);
+    }
+  }
+  for (int32_t i = t; i < n; i += kTailT) x[(int64_t)i * K] = xl[i];
+}
+
+template <class V, int W, int NB, bool Stream>
+__global__ void __launch_bounds__(kTailT) k_tail(TailJob<V> J) {
+  tail_run<V, W, NB, Stream>(J, (int32_t)blockIdx.x);
+}
+
+// Grouped: job blockIdx.x / kBatch of the list, vector blockIdx.x % kBatch.
+template <class V, int W, int NB, bool Stream>
+__global__ void __launch_bounds__(kTailT) k_gtail(const TailJob<V>* __restrict__ jobs,
+                                                  const int32_t* __restrict__ members,
+                                                  const int32_t* __restrict__ active) {
+  const int32_t i = uniform((int32_t)blockIdx.x / kBatch);
+  if (!active[members[i]]) return;
+  const TailJob<V> J = jobs[i];
+  tail_run<V, W, NB, Stream>(J, (int32_t)blockIdx.x % kBatch);
+}
+
+// b_c = P^T r (or b_c given, when the job has no P^T) and x_c = A_c^-1 b_c in
+// double: row i is the sum over k ascending of (A_c^-1 e_k)_i b_k.  A workgroup
+// solves J.rows rows of one vector: it restricts the whole vector itself (a
+// few hundred short rows, one lane each: cheaper than a launch to do it once)
+// while its columns of the inverse load, writes their products to LDS, and adds
+// each row's products on one lane, two instructions a term.
+constexpr int kCoarseAhead = 16;           // columns read from LDS ahead of their additions
+constexpr int kCoarseM = 16;               // elements of the inverse a thread loads: coarse_rows(n) n / kTailT at most
+constexpr int kCoarseStage = 8;            // elements of the residual a thread has in flight
+constexpr int kCoarseChunk = 16;           // entries of a row of P^T whose loads are in flight together
+// two wavefronts per SIMD: registers for those loads (left to itself the
+// compiler keeps eight wavefronts and loads one entry after the other)
+#define GMG_COARSE_BOUNDS __launch_bounds__(kTailT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__host__ __device__ constexpr int32_t coarse_up(int32_t n) { return (n + kCoarseAhead - 1) / kCoarseAhead * kCoarseAhead; }
+
+template <class V, int R>
+__device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group, int32_t vec) {
+  extern __shared__ double lds_raw[];
+  const int32_t n = J.n, K = J.stride, t = threadIdx.x;
+  double* bc = lds_raw;                    // [n]
+  const int32_t up = coarse_up(n);         // columns, rounded up
+  double* m = lds_raw + up;                // [up][R]
+  const int32_t i0 = group * R;
+  const int64_t ld = inv_ld(n);
+  const int32_t total = n * R;
+  // all loads that need no other first: the columns of the inverse (at most
+  // kCoarseM a thread, see coarse_rows) and the row's place in P^T
+  double a[kCoarseM];
+  const bool fused = J.T.ptr != nullptr;
+  const int32_t ti = min(t, n - 1);
+  SellRow row{};
+  if (fused) row = sell_row(J.T, ti);
+#pragma unroll
+  for (int u = 0; u < kCoarseM; ++u) {
+    if (u * kTailT >= total) continue;
+    const int32_t e = min(u * kTailT + t, total - 1);
+    a[u] = J.M[(int64_t)(e / R) * ld + min(i0 + (e & (R - 1)), n - 1)];
+  }
+  if (fused) {
+    // the residual in LDS where it fits: a row gathers some 22 of its entries,
+    // each a cache line of its own from memory
+    const V* r = J.r + vec;
+    auto restrict_rows = [&](const auto* x, int32_t stride) {
+      for (int32_t i = t; i < n; i += kTailT) {
+        if (i != t) row = sell_row(J.T, i);
+        bc[i] = (double)row_sum_at<kCoarseChunk>(J.T, row, x, stride);
+      }
+    };
+    if (J.staged) {
+      V* rl = reinterpret_cast<V*>(m + up * R);
+      for (int32_t e0 = 0; e0 < J.nf; e0 += kCoarseStage * kTailT) {
+        V v[kCoarseStage];
+#pragma unroll
+        for (int u = 0; u < kCoarseStage; ++u)
+          if (e0 + u * kTailT < J.nf) v[u] = r[(int64_t)min(e0 + u * kTailT + t, J.nf - 1) * K];
+#pragma unroll
+        for (int u = 0; u < kCoarseStage; ++u)
+          if (e0 + u * kTailT + t < J.nf) rl[e0 + u * kTailT + t] = v[u];
+      }
+      __syncthreads();
+      restrict_rows((const __attribute__((address_space(3))) V*)rl, 1);
+    } else {
+      restrict_rows(r, K);
+    }
+  } else {
+    const V* b = J.b + vec;
+    for (int32_t i = t; i < n; i += kTailT) bc[i] = (double)b[(int64_t)i * K];
+  }
+  __syncthreads();
+  // the row's products, which one lane then only has to add; columns up to a
+  // multiple of kCoarseAhead are zero (they leave a sum unchanged)
+#pragma unroll
+  for (int u = 0; u < kCoarseM; ++u) {
+    const int32_t e = u * kTailT + t;
+    if (e < total) m[e] = a[u] * bc[e / R];
+  }
+  if (total + t < up * R) m[total + t] = 0.0;
+  __syncthreads();
+  if (t < R && i0 + t < n) {
+    double acc = 0.0;
+    const double* p = m + t;
+    double q[2][kCoarseAhead];
+#pragma unroll
+    for (int u = 0; u < kCoarseAhead; ++u) q[0][u] = p[u * R];
+    for (int32_t k = 0; k < up; k += 2 * kCoarseAhead) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        // the block after this one (past the end: the first again, not added)
+        p = k + (h + 1) * kCoarseAhead < up ? p + kCoarseAhead * R : m + t;
+#pragma unroll
+        for (int u = 0; u < kCoarseAhead; ++u) q[1 - h][u] = p[u * R];
+        if (h == 0 || k + kCoarseAhead < up) {
+#pragma unroll
+          for (int u = 0; u < kCoarseAhead; ++u) acc = acc + q[h][u];
+        }
+      }
+    }
+    J.x[vec + (int64_t)(i0 + t) * K] = (V)acc;
+  }
+}
+
+template <class V, int R>
+__global__ void GMG_COARSE_BOUNDS k_coarse(CoarseJob<V> J) {
+  coarse_run<V, R>(J, (int32_t)blockIdx.x, (int32_t)blockIdx.y);
+}
+
+// The members' jobs of J.rows == R.
+template <class V, int R>
+__global__ void GMG_COARSE_BOUNDS k_gcoarse(const CoarseJob<V>* __restrict__ jobs,
+                                                    const GTile* __restrict__ tiles,
+                                                    const int32_t* __restrict__ active) {
+  const GTile g = tiles[blockIdx.x];
+  if (!active[g.member]) return;
+  const CoarseJob<V> J = jobs[g.job];
+  coarse_run<V, R>(J, g.tile, (int32_t)blockIdx.y);
+}
+
+// A_l (SELL, double) into the chunks' layout with values in V, a wavefront per
+// chunk: its place in the colours, then a row per lane, padding with the zero
+// behind the iterate and value 0.
+template <class V, int W>
+__global__ void __launch_bounds__(kBlock) k_tail_fill(SellView A, const int32_t* __restrict__ cptr, int32_t C, int32_t n,
+                                                      int32_t nchunk, int4* __restrict__ chunk,
+                                                      int32_t* __restrict__ info, u32x4* __restrict__ col,
+                                                      V* __restrict__ val) {
+  constexpr int E = TailBuf<V, W>::E;
+  const int32_t q = uniform((int32_t)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+  if (q >= nchunk) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t c = 0, before = 0, lo = 0, hi = 0;       // the colour that holds chunk q
+  for (; c < C; ++c) {
+    lo = cptr[c];
+    hi = cptr[c + 1];
+    const int32_t m = (hi - lo + kWave - 1) / kWave;
+    if (q < before + m) break;
+    before += m;
+  }
+  const int32_t r0 = lo + (q - before) * kWave, rows = min(hi - r0, kWave), r = r0 + lane;
+  const bool on = lane < rows;
+  const int32_t len = on ? A.len[r] : 0;
+  int32_t w = len;
+  for (int o = kWave / 2; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o, kWave));
+  w = min((w + 7) & ~7, W);
+  if (lane == 0) chunk[q] = int4{r0, rows, c, w};
+  const int64_t base = on ? A.ptr[r / kSlice] + (r & (kSlice - 1)) : 0;
+  int32_t dp = 0xFF;
+#pragma unroll
+  for (int e0 = 0; e0 < W; e0 += 8) {
+    uint32_t o[8];
+    V v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int32_t e = e0 + u;
+      int32_t j = e < len ? A.col[base + (int64_t)e * kSlice] : n;
+      v[u] = e < len ? (V)A.val[base + (int64_t)e * kSlice] : V(0);
+      if (e < len && j == r) {
+        dp = e;
+        j = n;
+      }
+      o[u] = (uint32_t)j * (uint32_t)sizeof(V);
+    }
+    u32x4 cw;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cw[u] = o[2 * u] | o[2 * u + 1] << 16;
+    col[((int64_t)q * (W / 8) + e0 / 8) * kWave + lane] = cw;
+#pragma unroll
+    for (int h = 0; h < 8 / E; ++h)
+#pragma unroll
+      for (int u = 0; u < E; ++u) val[(((int64_t)q * (W / E) + e0 / E + h) * kWave + lane) * E + u] = v[h * E + u];
+  }
+  if (on) info[r] = len << 8 | dp;
+}
+
+// Row buffers of a wavefront: what a thread's 256 registers take beside the
+// gathered values.  A level whose chunks all have one stays resident; the
+// streaming form has fewer, since a buffer being refilled needs registers twice.
+template <class V, int W, bool Stream>
+constexpr int tail_buffers() {
+  if (sizeof(V) == 8) return W == 8 ? (Stream ? 4 : 7) : W == 16 ? (Stream ? 2 : 3) : 2;
+  return W == 8 ? (Stream ? 4 : 8) : W == 16 ? (Stream ? 4 : 6) : (Stream ? 2 : 3);
+}
+
+// Calls f(W, NB, Stream) as integral constants for levels of nchunk chunks (the
+// most of a group) and row width W.
+template <class V, class F>
+void with_tail(int32_t W, int32_t nchunk, F&& f) {
+  auto go = [&](auto WC) {
+    constexpr int w = decltype(WC)::value;
+    const std::integral_constant<int, tail_buffers<V, w, false>()> resident;
+    {
+      if (nchunk > resident.value * (kTailT / kWave)) {
+        f(WC, std::integral_constant<int, tail_buffers<V, w, true>()>{}, std::integral_constant<bool, true>{});
+        return;
+      }
+    }
+    f(WC, resident, std::integral_constant<bool, false>{});
+  };
+  switch (W) {
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    case 16: go(std::integral_constant<int, 16>{}); break;
+    default: go(std::integral_constant<int, 32>{}); break;
+  }
+}
+
+}  // namespace
+
+int32_t tail_width(int32_t maxlen) { return maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : kTailWMax; }
+
+template <class V>
+size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc) {
+  return (size_t)tail_lds<V>(n) + std::max((size_t)A.nchunk * sizeof(int4), (size_t)nc * sizeof(V));
+}
+
+template <class V>
+TailJob<V> tail_job(const LevelViewT<V>& v, int32_t stride) {
+  TailJob<V> J;
+  J.n = v.n;
+  J.ncolors = v.ncolors;
+  J.stride = stride;
+  J.maxlen = v.maxa;
+  J.A = v.R;
+  J.S = v.A;
+  J.diag = v.diag;
+  J.b = v.b;
+  J.x = v.x;
+  return J;
+}
+
+template <class V>
+TailJob<V> tail_pre_job(const LevelViewT<V>& v, int32_t stride, int32_t nu, int32_t skip) {
+  TailJob<V> J = tail_job(v, stride);
+  J.nsweeps = nu;
+  J.skip = nu > 0 ? skip : 0;
+  J.r = v.r;
+  return J;
+}
+
+template <class V>
+TailJob<V> tail_post_job(const LevelViewT<V>& v, const LevelViewT<V>& c, int32_t stride, int32_t nu,
+                         bool descending) {
+  TailJob<V> J = tail_job(v, stride);
+  J.nsweeps = nu;
+  J.descending = descending ? 1 : 0;
+  J.q_col = v.q_col;
+  J.q_val = v.q_val;
+  J.q_cnt = v.q_cnt;
+  J.xc = c.x;
+  J.nc = c.n;
+  return J;
+}
+
+template <class V>
+void tail_sweeps(const TailJob<V>& J, int32_t W, int32_t vectors, hipStream_t s) {
+  if (!J.A.col || W != tail_width(J.maxlen) || J.n > kTailRows)
+    throw Error{GMG_DEVICE_ERROR, "tail level without its row layout"};
+  with_tail<V>(W, J.A.nchunk, [&](auto WC, auto BC, auto SC) {
+    k_tail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value>
+        <<<vectors, kTailT, tail_lds_bytes(J.A, J.n, J.nc), s>>>(J);
+  });
+}
+
+template <class V>
+void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t W, int32_t nchunk, size_t lds,
+                  const int32_t* active, hipStream_t s) {
+  if (count <= 0) return;
+  with_tail<V>(W, nchunk, [&](auto WC, auto BC, auto SC) {
+    k_gtail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value><<<count * kBatch, kTailT, lds, s>>>(jobs, members, active);
+  });
+}
+
+// Rows a workgroup of the coarsest solve takes: kCoarseM elements of the inverse
+// a thread, at most 64 KiB in LDS.  More rows per workgroup mean fewer copies of
+// the restriction, fewer mean more load paths.
+int32_t coarse_rows(int64_t n) { return n <= 512 ? 16 : n <= 1024 ? 8 : n <= 2048 ? 4 : 2; }
+template <class V>
+size_t coarse_lds(const CoarseJob<V>& J) {
+  return (size_t)coarse_up(J.n) * 8 * (1 + J.rows) + (J.staged ? (size_t)J.nf * sizeof(V) : 0);
+}
+
+
+template <class F>
+void with_rows(int32_t R, F&& f) {
+  switch (R) {
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    default: f(std::integral_constant<int, 2>{}); break;
+  }
+}
+
+template <class V>
+void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
+  with_rows(J.rows, [&](auto RC) {
+    k_coarse<V, decltype(RC)::value><<<dim3((J.n + J.rows - 1) / J.rows, vectors), kTailT, coarse_lds(J), s>>>(J);
+  });
+}
+
+template <class V>
+void gcoarse_fused(const CoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, int32_t rows, size_t lds,
+                   const int32_t* active, hipStream_t s) {
+  if (ntiles <= 0) return;
+  with_rows(rows, [&](auto RC) {
+    k_gcoarse<V, decltype(RC)::value><<<dim3(ntiles, kBatch), kTailT, lds, s>>>(jobs, tiles, active);
+  });
+}
+
+template <class V>
+void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s) {
+  auto go = [&](auto WC) {
+    k_tail_fill<V, decltype(WC)::value><<<blocks_for(nchunk, kBlock / kWave), kBlock, 0, s>>>(
+        v.A, v.cptr, v.ncolors, v.n, nchunk, chunk, info, reinterpret_cast<u32x4*>(col), val);
+  };
+  switch (tail_width(v.maxa)) {
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    case 16: go(std::integral_constant<int, 16>{}); break;
+    default: go(std::integral_constant<int, 32>{}); break;
+  }
+}
+
+#define GMG_INSTANTIATE_TAIL(V)                                                                                 \
+  template size_t tail_lds_bytes<V>(const TailRows<V>&, int32_t, int32_t);                                                               \
+  template TailJob<V> tail_pre_job<V>(const LevelViewT<V>&, int32_t, int32_t, int32_t);                        \
+  template TailJob<V> tail_post_job<V>(const LevelViewT<V>&, const LevelViewT<V>&, int32_t, int32_t, bool);    \
+  template void tail_sweeps<V>(const TailJob<V>&, int32_t, int32_t, hipStream_t);                              \
+  template void gtail_sweeps<V>(const TailJob<V>*, const int32_t*, int32_t, int32_t, int32_t, size_t, const int32_t*,   \
+                                hipStream_t);                                                                  \
+  template size_t coarse_lds<V>(const CoarseJob<V>&);                                                          \
+  template void coarse_fused<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                    \
+  template void gcoarse_fused<V>(const CoarseJob<V>*, const GTile*, int32_t, int32_t, size_t, const int32_t*,  \
+                                 hipStream_t);                                                                 \
+  template void tail_fill<V>(const LevelView&, int32_t, int4*, int32_t*, uint16_t*, V*, hipStream_t);
+GMG_INSTANTIATE_TAIL(double)
+GMG_INSTANTIATE_TAIL(float)
+#undef GMG_INSTANTIATE_TAIL
+
+}  // namespace gmg
