@@ -16,20 +16,18 @@ namespace {
 constexpr int K = kBatch;
 constexpr int kChunkMulti = 8;
 
-// sum_t val[t] * x[col[t] * K + q] in entry order, skipping column `skip`
-// (branch-free loads as in row_sum_seq; every row has at least one entry).
+// sum_t val[t] * x[col[t] * K + q] in entry order, skipping column `skip` (loads
+// as in row_sum_seq, up to the longest of the wavefront's rows).
 template <class V>
 __device__ __forceinline__ V row_sum_multi(const Sell<V>& A, int32_t r, const V* x, int32_t skip, int q) {
-  const int32_t len = A.len[r];
-  const int32_t base = A.ptr[r / kSlice] + (r & (kSlice - 1));
+  const SellRow R = sell_row(A, r);
   V acc = V(0);
-  int32_t t0 = 0;
-  do {
+  for (int32_t t0 = 0; __ballot(t0 < R.len) != 0; t0 += kChunkMulti) {
     int32_t j[kChunkMulti];
     V v[kChunkMulti], xv[kChunkMulti];
 #pragma unroll
     for (int u = 0; u < kChunkMulti; ++u) {
-      const int32_t o = base + min(t0 + u, len - 1) * kSlice;
+      const int32_t o = R.base + min(t0 + u, R.width - 1) * kSlice;
       j[u] = A.col[o];
       v[u] = A.val[o];
     }
@@ -37,9 +35,8 @@ __device__ __forceinline__ V row_sum_multi(const Sell<V>& A, int32_t r, const V*
     for (int u = 0; u < kChunkMulti; ++u) xv[u] = x[(int64_t)j[u] * K + q];
 #pragma unroll
     for (int u = 0; u < kChunkMulti; ++u)
-      if (t0 + u < len && j[u] != skip) acc = acc + v[u] * xv[u];
-    t0 += kChunkMulti;
-  } while (t0 < len);
+      if (t0 + u < R.len && j[u] != skip) acc = acc + v[u] * xv[u];
+  }
   return acc;
 }
 
