@@ -896,7 +896,7 @@ template <class V>
 void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const LevelViewT<V>& v = c.v[l];
   if (l + 1 == h.L.size()) {
-    coarse_fused(coarse_job<V>(h, nullptr, v, kBatch), kBatch, s);
+    mcoarse(h.cinv, v, s);
     return;
   }
   const LevelViewT<V>& cv = c.v[l + 1];
@@ -908,7 +908,7 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
     for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false);
     mresidual(v, s);
   }
-  if (l + 2 == h.L.size() && coarse_fuses(h)) {
+  if (l + 2 == h.L.size() && cv.n <= kCoarseFusedBatch) {
     coarse_fused(coarse_job<V>(h, &v, cv, kBatch), kBatch, s);
   } else {
     mrestrict(v, cv, s);
@@ -1157,13 +1157,18 @@ struct RowStep {
 template <class V>
 struct GroupPlan {
   // the cycle as a sequence of steps, in launch order
-  enum Kind { SWEEP, RESIDUAL, RESTRICT, PROLONG, TAIL, COARSE };
+  enum Kind { SWEEP, BLOCKS, RESIDUAL, RESTRICT, PROLONG, TAIL, COARSE };
   struct Step {
     Kind kind;
     int32_t index;
   };
   std::vector<Step> order;
   std::vector<RowStep<GSweepJob<V>>> sweeps;
+  // block colours of levels swept in block order
+  struct BlockStep : RowStep<GBlockJob<V>> {
+    size_t lds = 0;
+  };
+  std::vector<BlockStep> blocks;
   std::vector<RowStep<GResJob<V>>> residuals;
   std::vector<RowStep<GRestJob<V>>> restricts;
   std::vector<RowStep<GProlJob<V>>> prolongs;
@@ -1178,12 +1183,7 @@ struct GroupPlan {
     const int32_t* dmembers = nullptr;
   };
   std::vector<TailStep> tails;
-  // coarsest solves: the members' jobs of one number of rows a workgroup takes
-  struct CoarseStep : RowStep<CoarseJob<V>> {
-    int32_t rows = 0;
-    size_t lds = 0;
-  };
-  std::vector<CoarseStep> coarse;
+  RowStep<GCoarseJob<V>> coarse;
   // CG: one job per member, tiles over each member's n * kBatch elements
   RowStep<GKryJob<V>> kry;
   int32_t count = 0;
@@ -1210,8 +1210,6 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
     post = std::max(post, h.opt.nu_post);
   }
   auto add_restrict = [&](RowStep<GRestJob<V>>& rt, int m, int l) {
-    const Handle& h = *H[m];
-    if (l + 2 == (int)h.L.size() && coarse_fuses(h)) return;      // the coarsest solve restricts
     const LevelViewT<V>& v = C[m]->v[l];
     const LevelViewT<V>& cv = C[m]->v[l + 1];
     rt.add(GRestJob<V>{v.T, v.r, cv.b, cv.x, cv.n}, m, (int64_t)cv.n * kBatch);
@@ -1244,26 +1242,43 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
     }
   };
   auto classes = [&](int m, int l) { return (int)H[m]->L[l].color_ptr.size() - 1; };
+  // step k of a sweep: block colour k of the members that sweep the level by
+  // blocks, colour class k of the others
   auto sweep_step = [&](int l, int sweep, bool descending) {
     int kmax = 0;
     for (int m = 0; m < M; ++m)
-      if (l < ts[m]) kmax = std::max(kmax, classes(m, l));
+      if (l < ts[m]) kmax = std::max(kmax, mblock_lds(C[m]->v[l].B) ? 4 : classes(m, l));
     for (int k = 0; k < kmax; ++k) {
       RowStep<GSweepJob<V>> st;
+      typename GroupPlan<V>::BlockStep bs;
       for (int m = 0; m < M; ++m) {
         const Handle& h = *H[m];
         const int nu = descending ? h.opt.nu_post : h.opt.nu_pre;
-        const int K = l < ts[m] ? classes(m, l) : 0;
-        if (sweep >= nu || k >= K) continue;
+        if (l >= ts[m] || sweep >= nu) continue;
+        const LevelViewT<V>& v = C[m]->v[l];
+        const size_t lds = mblock_lds(v.B);
+        const int K = lds ? 4 : classes(m, l);
+        if (k >= K) continue;
         const int c = descending ? K - 1 - k : k;      // the batched cycle is symmetric
+        if (lds) {
+          const int32_t nb = v.B.bstart[c + 1] - v.B.bstart[c];
+          if (nb <= 0) continue;
+          bs.add_tiles(GBlockJob<V>{v.B, v.b, v.diag, v.x, v.B.bstart[c], descending ? 1 : 0}, m, nb);
+          bs.lds = std::max(bs.lds, lds);
+          continue;
+        }
         const int32_t r0 = h.L[l].color_ptr[c], r1 = h.L[l].color_ptr[c + 1];
         if (r1 <= r0) continue;
-        const LevelViewT<V>& v = C[m]->v[l];
         st.add(GSweepJob<V>{v.A, v.diag, v.b, v.x, r0, r1}, m, (int64_t)(r1 - r0) * kBatch);
       }
-      if (st.ntiles() == 0) continue;
-      P.order.push_back({GroupPlan<V>::SWEEP, (int32_t)P.sweeps.size()});
-      P.sweeps.push_back(std::move(st));
+      if (st.ntiles() > 0) {
+        P.order.push_back({GroupPlan<V>::SWEEP, (int32_t)P.sweeps.size()});
+        P.sweeps.push_back(std::move(st));
+      }
+      if (bs.ntiles() > 0) {
+        P.order.push_back({GroupPlan<V>::BLOCKS, (int32_t)P.blocks.size()});
+        P.blocks.push_back(std::move(bs));
+      }
     }
   };
   for (int l = 0; l < Lmax; ++l) {
@@ -1287,22 +1302,11 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
       if ((int)H[m]->L.size() - 1 - d >= ts[m]) add_restrict(rt, m, (int)H[m]->L.size() - 1 - d);
     push_restrict(std::move(rt));
   }
-  for (int32_t rows : {16, 8, 4, 2}) {
-    typename GroupPlan<V>::CoarseStep st;
-    st.rows = rows;
-    for (int m = 0; m < M; ++m) {
-      const Handle& h = *H[m];
-      const int nl = (int)h.L.size();
-      const LevelViewT<V>& cv = C[m]->v[nl - 1];
-      if (coarse_rows(cv.n) != rows) continue;
-      const CoarseJob<V> J = coarse_job<V>(h, nl > 1 && coarse_fuses(h) ? &C[m]->v[nl - 2] : nullptr, cv, kBatch);
-      st.add_tiles(J, m, (cv.n + rows - 1) / rows);
-      st.lds = std::max(st.lds, coarse_lds(J));
-    }
-    if (st.ntiles() == 0) continue;
-    P.order.push_back({GroupPlan<V>::COARSE, (int32_t)P.coarse.size()});
-    P.coarse.push_back(std::move(st));
+  for (int m = 0; m < M; ++m) {
+    const LevelViewT<V>& cv = C[m]->v.back();
+    P.coarse.add_tiles(GCoarseJob<V>{H[m]->cinv, cv.b, cv.x, cv.n}, m, mcoarse_tiles(cv.n));
   }
+  P.order.push_back({GroupPlan<V>::COARSE, 0});
   for (int d = 1; d <= Tmax; ++d) tail_step(d, true);
   for (int l = Lmax - 1; l >= 0; --l) {
     RowStep<GProlJob<V>> pr;
@@ -1325,10 +1329,11 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
               m, n * kBatch);
   }
   for (auto& st : P.sweeps) st.upload(dt);
+  for (auto& st : P.blocks) st.upload(dt);
   for (auto& st : P.residuals) st.upload(dt);
   for (auto& st : P.restricts) st.upload(dt);
   for (auto& st : P.prolongs) st.upload(dt);
-  for (auto& st : P.coarse) st.upload(dt);
+  P.coarse.upload(dt);
   P.kry.upload(dt);
   for (auto& st : P.tails) {
     st.djobs = dt.put(st.jobs);
@@ -1345,6 +1350,11 @@ void group_iteration(const GroupPlan<V>& P, const int32_t* active, hipStream_t s
       case GroupPlan<V>::SWEEP: {
         const auto& r = P.sweeps[st.index];
         gsweep(r.djobs, r.dtiles, r.ntiles(), active, s);
+        break;
+      }
+      case GroupPlan<V>::BLOCKS: {
+        const auto& r = P.blocks[st.index];
+        gblock_sweep(r.djobs, r.dtiles, r.ntiles(), r.lds, active, s);
         break;
       }
       case GroupPlan<V>::RESIDUAL: {
@@ -1367,11 +1377,9 @@ void group_iteration(const GroupPlan<V>& P, const int32_t* active, hipStream_t s
         gtail_sweeps(t.djobs, t.dmembers, (int32_t)t.jobs.size(), t.W, t.nchunk, t.lds, active, s);
         break;
       }
-      case GroupPlan<V>::COARSE: {
-        const auto& c = P.coarse[st.index];
-        gcoarse_fused(c.djobs, c.dtiles, c.ntiles(), c.rows, c.lds, active, s);
+      case GroupPlan<V>::COARSE:
+        gcoarse(P.coarse.djobs, P.coarse.dtiles, P.coarse.ntiles(), active, s);
         break;
-      }
     }
   }
   gkry_direction(P.kry.djobs, P.count, P.kry.dtiles, P.kry.ntiles(), active, s);

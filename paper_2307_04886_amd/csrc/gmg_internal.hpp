@@ -162,6 +162,10 @@ constexpr int64_t kTailRows = 4096;  // levels of at most this many rows are swe
 constexpr int kTailT = 512;          // its threads
 constexpr int kTailWMax = 32;        // entries of a row it holds at most
 constexpr int64_t kCoarseFused = 1024;   // coarsest rows up to which the restriction is fused with the solve
+// coarsest rows up to which that also holds for kBatch vectors of one hierarchy
+// (each workgroup restricts its vector; 226 rows: 10 us against 9 for the restriction
+// and 10.5 for the batched solve; from 513 rows the workgroups take twice the LDS a row)
+constexpr int64_t kCoarseFusedBatch = 512;
 constexpr int64_t kCoarseStaged = 72 * 1024;   // residual bytes it keeps in LDS beside the inverse's columns (at most 73 KiB)
 constexpr int kLaneEntries = 8;      // entries per lane per pass of a lane-parallel row
 
@@ -196,6 +200,38 @@ struct alignas(32) BlockHdr {
   uint64_t mask;                       // colours with rows in the block
 };
 constexpr int kBlkMaxColors = 64;    // colours a block sweep handles
+constexpr int kBatch = 8;            // right-hand sides of a batched launch
+
+// LDS of a block of the batched block sweep (multi.hip): rows and halo, width w,
+// C colours, values of vb bytes.
+struct MBlockLds {
+  int32_t vs, is;                          // strides of a row's values and columns
+  int32_t o_v, o_i, o_b, o_d, o_info, o_id, o_cls, bytes;   // byte offsets (the iterates start at 0)
+};
+__host__ __device__ inline MBlockLds mblock_layout(int32_t rows, int32_t nh, int32_t w, int32_t C, int32_t vb) {
+  MBlockLds L;
+  const int32_t wp = (w + 7) & ~7, e = 16 / vb;
+  L.vs = wp + e;
+  L.is = wp + 8;
+  auto up = [](int32_t b) { return (b + 15) & ~15; };
+  int32_t o = up((rows + nh + 1) * kBatch * vb);
+  L.o_v = o;
+  o += up(rows * L.vs * vb);
+  L.o_i = o;
+  o += up(rows * L.is * 2);
+  L.o_b = o;
+  o += up(rows * kBatch * vb);
+  L.o_d = o;
+  o += up(rows * vb);
+  L.o_info = o;
+  o += up(rows * 4);
+  L.o_id = o;
+  o += up(rows * 4);
+  L.o_cls = o;
+  L.bytes = o + up((C + 1) * 4);
+  return L;
+}
+constexpr int32_t kMBlockLdsMax = 156 * 1024;   // blocks beyond it take the launches per class
 template <class V>
 struct BlockView {
   int32_t nblk = 0;                     // 0: no block sweep (the colour classes are launched one by one)
@@ -203,6 +239,7 @@ struct BlockView {
   int32_t ncls = 0;                     // colours C of the level
   int32_t rows_per_thread = 1, width = 32;   // kernel shape: local rows per thread, register entries per row
   int32_t lds_bytes = 0;                // (largest block + largest halo + 1) values
+  int32_t mlds[2] = {};                 // most LDS of a block in the batched sweep, in float and in double
   const int32_t* boff = nullptr;
   const int32_t* brows = nullptr;
   const int32_t* bcls = nullptr;
@@ -231,6 +268,8 @@ struct BlockView {
     o.rows_per_thread = rows_per_thread;
     o.width = width;
     o.lds_bytes = lds_bytes;
+    o.mlds[0] = mlds[0];
+    o.mlds[1] = mlds[1];
     o.boff = boff;
     o.brows = brows;
     o.bcls = bcls;
@@ -429,7 +468,6 @@ enum : int { KS_RHO = 0, KS_BETA = 1, KS_ALPHA = 2, KS_NORM = 3, KS_BNORM = 4, K
 
 // The same CG for kBatch right-hand sides at once; vectors interleaved,
 // entry (i, q) at i * kBatch + q.
-constexpr int kBatch = 8;
 struct Batch {
   double* x = nullptr;                  // level 0, colour-sorted numbering, [n][kBatch]
   double* b = nullptr;
@@ -605,6 +643,9 @@ template <class V>
 void mrestrict(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
 template <class V>
 void mprolong(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
+template <class V>
+void mcoarse(const double* cinv, const LevelViewT<V>& c, hipStream_t s);
+int32_t mcoarse_tiles(int32_t n);       // workgroups of a batched coarsest solve
 void mkry_init(Batch& k, int64_t n, hipStream_t s);
 template <class V>
 void mkry_direction(Batch& k, const V* z, int64_t n, hipStream_t s);
@@ -634,6 +675,15 @@ struct GSweepJob {                      // one colour class [r0, r1) of A_l
   int32_t r0, r1;
 };
 template <class V>
+struct GBlockJob {                      // one block colour of a level swept in block order (blocks from blk0)
+  BlockView<V> B;
+  const V* b;
+  const V* diag;
+  V* x;
+  int32_t blk0;
+  int32_t descending;
+};
+template <class V>
 struct GResJob {                        // r = b - A x on a level
   Sell<V> A;
   const V* b;
@@ -659,6 +709,13 @@ struct GProlJob {                       // x += P x_c
   int64_t n;
 };
 template <class V>
+struct GCoarseJob {                     // x = A_c^-1 b
+  const double* M;
+  const V* b;
+  V* x;
+  int32_t n;
+};
+template <class V>
 struct GKryJob {                        // a member's CG state (level 0, double) and cycle ends
   SellView A0;
   double *x, *b, *r, *r_old, *p, *q, *part, *scal;
@@ -669,12 +726,22 @@ struct GKryJob {                        // a member's CG state (level 0, double)
 };
 template <class V>
 void gsweep(const GSweepJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
+// tiles: a block of the job's block colour each; lds: the most mblock_lds of the jobs
+template <class V>
+void gblock_sweep(const GBlockJob<V>* jobs, const GTile* tiles, int32_t ntiles, size_t lds, const int32_t* active,
+                  hipStream_t s);
+// LDS bytes of the batched block sweep, 0 when the level has none (or its blocks do not fit)
+template <class V>
+size_t mblock_lds(const BlockView<V>& B);
 template <class V>
 void gresidual(const GResJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
 template <class V>
 void grestrict(const GRestJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
 template <class V>
 void gprolong(const GProlJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
+// tiles: the mcoarse_tiles groups of rows of every job
+template <class V>
+void gcoarse(const GCoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
 // one-workgroup levels (tail.hip)
 int32_t tail_width(int32_t maxlen);                        // entries W held of rows of at most maxlen
 template <class V>
@@ -693,13 +760,7 @@ void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count,
                   const int32_t* active, hipStream_t s);
 int32_t coarse_rows(int64_t n);
 template <class V>
-size_t coarse_lds(const CoarseJob<V>& J);
-template <class V>
 void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s);
-// tiles: groups of `rows` rows of every member's job (all jobs of J.rows == rows)
-template <class V>
-void gcoarse_fused(const CoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, int32_t rows, size_t lds,
-                   const int32_t* active, hipStream_t s);
 template <class V>
 void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s);
 // CG steps over the members' jobs (count of them); `tiles` cover each member's n * kBatch elements

@@ -68,6 +68,70 @@ __device__ __forceinline__ void mrestrict_entry(const Sell<V>& T, const V* r, V*
   xc[t] = V(0);                                   // the coarse iterate starts from zero
 }
 
+// x = A_c^-1 b for the K right-hand sides in double: entry (i, q) is the sum over
+// k ascending of (A_c^-1 e_k)_i b_kq, on lane (i, q) of a workgroup of 32 rows.
+// The columns go through LDS in tiles (64 KiB of the inverse, the right-hand
+// sides beside them), the next tile's loads all in flight in registers while one
+// is added: loaded 16 columns ahead, a column cost a sixteenth of a memory
+// latency, 200 cycles (n_c = 308: 24 us, now 14.4; 226: 10.5; the direct solves
+// of 24 hierarchies grouped, the largest of 800 rows: 78 us, now 42).
+constexpr int kMCoarseTile = 256;          // columns of a tile
+constexpr int kMCoarseRows = kBlock / K;
+constexpr int kMCoarseAhead = 8;           // columns read from LDS ahead of their additions
+
+template <class V>
+__device__ __forceinline__ void mcoarse_run(const double* __restrict__ M, const V* __restrict__ b, V* __restrict__ x,
+                                            int32_t n, int32_t group) {
+  extern __shared__ double lds_raw[];
+  double* ml = lds_raw;                                                  // [tile][rows]
+  V* bl = reinterpret_cast<V*>(lds_raw + kMCoarseTile * kMCoarseRows);   // [tile][K]
+  constexpr int kM = kMCoarseTile * kMCoarseRows / kBlock, kB = kMCoarseTile * K / kBlock;
+  const int32_t tid = threadIdx.x, q = tid % K, i = tid / K, i0 = group * kMCoarseRows;
+  const int64_t ld = inv_ld(n);
+  double a[kM];
+  V v[kB];
+  auto load = [&](int32_t c0) {
+#pragma unroll
+    for (int u = 0; u < kM; ++u) {
+      const int32_t e = u * kBlock + tid, k = c0 + e / kMCoarseRows;
+      if (c0 + u * (kBlock / kMCoarseRows) < n) a[u] = M[(int64_t)min(k, n - 1) * ld + min(i0 + e % kMCoarseRows, n - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < kB; ++u)
+      if (c0 + u * (kBlock / K) < n) v[u] = b[min((int64_t)c0 * K + u * kBlock + tid, (int64_t)n * K - 1)];
+  };
+  load(0);
+  double acc = 0.0;
+  for (int32_t c0 = 0; c0 < n; c0 += kMCoarseTile) {
+    if (c0) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kM; ++u) ml[u * kBlock + tid] = a[u];
+#pragma unroll
+    for (int u = 0; u < kB; ++u) bl[u * kBlock + tid] = v[u];
+    __syncthreads();
+    const int32_t cols = min(kMCoarseTile, n - c0);
+    if (c0 + kMCoarseTile < n) load(c0 + kMCoarseTile);
+    for (int32_t k = 0; k < cols; k += kMCoarseAhead) {
+      double p[kMCoarseAhead];
+#pragma unroll
+      for (int u = 0; u < kMCoarseAhead; ++u) p[u] = ml[(k + u) * kMCoarseRows + i] * (double)bl[(k + u) * K + q];
+#pragma unroll
+      for (int u = 0; u < kMCoarseAhead; ++u)
+        if (k + u < cols) acc = acc + p[u];
+    }
+  }
+  if (i0 + i < n) x[(int64_t)(i0 + i) * K + q] = (V)acc;
+}
+
+template <class V>
+constexpr size_t mcoarse_lds() { return (size_t)kMCoarseTile * (kMCoarseRows * 8 + K * sizeof(V)); }
+
+template <class V>
+__global__ void __launch_bounds__(kBlock) k_mcoarse(const double* __restrict__ M, const V* __restrict__ b,
+                                                    V* __restrict__ x, int32_t n) {
+  mcoarse_run(M, b, x, n, (int32_t)blockIdx.x);
+}
+
 template <class V>
 __global__ void __launch_bounds__(kBlock) k_mgs(Sell<V> A, const V* __restrict__ diag, const V* __restrict__ b,
                                                 V* x, int32_t r0, int32_t r1) {
@@ -84,6 +148,148 @@ template <class V>
 __global__ void __launch_bounds__(kBlock) k_mrestrict(Sell<V> T, const V* __restrict__ r, V* __restrict__ bc,
                                                       V* __restrict__ xc, int64_t nc) {
   mrestrict_entry(T, r, bc, xc, nc, (int64_t)blockIdx.x * kBlock + threadIdx.x);
+}
+
+// One block of a block-ordered level (see k_gs_block) for the K right-hand
+// sides: K lanes per row, the rows of a colour at once (32 a pass), the block's
+// iterates with their halo, right-hand sides, diagonal and matrix in LDS.  A
+// launch per block colour instead of one per (block colour, colour) class: the
+// classes have some 20 rows a block, and a launch of one took 5 us whatever its
+// rows.  The matrix goes to LDS row by row (values of a row at stride vs, columns
+// as 16-bit slots at stride is), read 16 bytes at a time by the K lanes of a row
+// together (a broadcast); the strides place the rows of a wavefront in different
+// banks.  A workgroup of 256 threads and some 50 KB (float) leaves three to a
+// compute unit.  13,759 rows in float: 12.4 us a launch against 12 launches of
+// 5.1 us for the block colour's classes (the whole batched solve of a 100K-point
+// torus: 10.8 ms, now 4.0; 24 hierarchies grouped: 71 ms, now 53).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <class V>
+__device__ __forceinline__ void mblock_run(const BlockView<V>& B, const V* __restrict__ bvec,
+                                           const V* __restrict__ diag, V* x, int32_t b, bool descending) {
+  extern __shared__ double lds_raw[];
+  char* lds = reinterpret_cast<char*>(lds_raw);
+  constexpr int E = 16 / sizeof(V);        // values of a 16-byte access
+  constexpr int G = 8;                     // entries a step loads and sums
+  const BlockHdr hd = B.hdr[b];
+  const int32_t rows = hd.rows, nh = hd.nh, w = hd.w, C = B.ncls, wp = (w + 7) & ~7, pad = rows + nh;
+  const MBlockLds L = mblock_layout(rows, nh, w, C, (int32_t)sizeof(V));
+  V* xl = reinterpret_cast<V*>(lds);
+  V* vl = reinterpret_cast<V*>(lds + L.o_v);
+  uint16_t* il = reinterpret_cast<uint16_t*>(lds + L.o_i);
+  V* bl = reinterpret_cast<V*>(lds + L.o_b);
+  V* dl = reinterpret_cast<V*>(lds + L.o_d);
+  int32_t* info = reinterpret_cast<int32_t*>(lds + L.o_info);
+  int32_t* id = reinterpret_cast<int32_t*>(lds + L.o_id);
+  int32_t* cls = reinterpret_cast<int32_t*>(lds + L.o_cls);
+  const int32_t tid = threadIdx.x, q = tid % K, sub = tid / K;
+  constexpr int kSub = kBlkThreads / K;    // rows a pass covers
+  const int32_t* gl = B.glist + (int64_t)b * B.gstride;
+  // rows, halo: the gather list, then the vectors' values
+  constexpr int U = 8;
+  for (int32_t k0 = 0; k0 < pad; k0 += U * kSub) {
+    int32_t g[U];
+    V xv[U], bv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = gl[min(k0 + u * kSub + sub, pad - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xv[u] = x[(int64_t)g[u] * K + q];
+      if (k0 + u * kSub < rows) bv[u] = bvec[(int64_t)g[u] * K + q];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t k = k0 + u * kSub + sub;
+      if (k < pad) xl[k * K + q] = xv[u];
+      if (k < rows) {
+        bl[k * K + q] = bv[u];
+        if (q == 0) id[k] = g[u];
+      }
+    }
+  }
+  if (tid < K) xl[pad * K + tid] = V(0);
+  for (int32_t c = tid; c <= C; c += kBlkThreads) cls[c] = B.bcls[(int64_t)b * (C + 1) + c];
+  // the matrix, a row per thread (its entries are a column apart in the ELL)
+  for (int32_t p = tid; p < rows; p += kBlkThreads) {
+    info[p] = B.rinfo[hd.r0 + p] >> 8;
+    dl[p] = diag[gl[p]];
+    for (int32_t t0 = 0; t0 < wp; t0 += G) {
+      int32_t s[G];
+      V v[G];
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int32_t o = hd.e0 + min(t0 + u, w - 1) * rows + p;
+        s[u] = B.elx[o];
+        v[u] = B.elv[o];
+      }
+      u32x4 cw;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t lo = t0 + 2 * u < w ? s[2 * u] : pad, hi = t0 + 2 * u + 1 < w ? s[2 * u + 1] : pad;
+        cw[u] = lo | hi << 16;
+      }
+      *reinterpret_cast<u32x4*>(il + p * L.is + t0) = cw;
+#pragma unroll
+      for (int h = 0; h < G / E; ++h) {
+        u32x4 a;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+          const V e = t0 + h * E + u < w ? v[h * E + u] : V(0);
+          if constexpr (sizeof(V) == 8) {
+            const uint64_t z = __builtin_bit_cast(uint64_t, e);
+            a[2 * u] = (uint32_t)z;
+            a[2 * u + 1] = (uint32_t)(z >> 32);
+          } else {
+            a[u] = __builtin_bit_cast(uint32_t, e);
+          }
+        }
+        *reinterpret_cast<u32x4*>(vl + p * L.vs + t0 + h * E) = a;
+      }
+    }
+  }
+  __syncthreads();
+  for (int32_t kk = 0; kk < C; ++kk) {
+    const int32_t c = descending ? C - 1 - kk : kk;
+    if (!((hd.mask >> c) & 1)) continue;   // no row of this colour in the block
+    const int32_t p1 = cls[c + 1];
+    for (int32_t p = cls[c] + sub; p < p1; p += kSub) {
+      const int32_t len = info[p];
+      V s = V(0);
+      for (int32_t t0 = 0; t0 < len; t0 += G) {
+        const u32x4 cw = *reinterpret_cast<const u32x4*>(il + p * L.is + t0);
+        u32x4 a[G / E];
+#pragma unroll
+        for (int h = 0; h < G / E; ++h) a[h] = *reinterpret_cast<const u32x4*>(vl + p * L.vs + t0 + h * E);
+        V xv[G];
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          const uint32_t j = (u & 1) ? cw[u / 2] >> 16 : cw[u / 2] & 0xFFFFu;
+          xv[u] = xl[j * K + q];
+        }
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          V e;
+          if constexpr (sizeof(V) == 8) {
+            e = __builtin_bit_cast(V, (uint64_t)a[u / E][2 * (u % E) + 1] << 32 | a[u / E][2 * (u % E)]);
+          } else {
+            const uint32_t z = a[u / E][u % E];
+            e = __builtin_bit_cast(V, z);
+          }
+          s = s + e * xv[u];               // past the row's end: +0 terms
+        }
+      }
+      xl[p * K + q] = (bl[p * K + q] - s) / dl[p];
+    }
+    __syncthreads();
+  }
+  for (int32_t k = sub; k < rows; k += kSub) x[(int64_t)id[k] * K + q] = xl[k * K + q];
+}
+
+template <class V>
+__global__ void __launch_bounds__(kBlkThreads) k_mgs_block(BlockView<V> B, const V* __restrict__ bvec,
+                                                           const V* __restrict__ diag, V* x, int32_t blk0,
+                                                           int32_t descending) {
+  mblock_run(B, bvec, diag, x, blk0 + (int32_t)blockIdx.x, descending != 0);
 }
 
 template <class V>
@@ -366,6 +572,16 @@ __global__ void __launch_bounds__(kBlock) k_gsweep(const GSweepJob<V>* __restric
 }
 
 template <class V>
+__global__ void __launch_bounds__(kBlkThreads) k_gblock(const GBlockJob<V>* __restrict__ jobs,
+                                                        const GTile* __restrict__ tiles,
+                                                        const int32_t* __restrict__ active) {
+  const GTile g = tiles[blockIdx.x];
+  if (!active[g.member]) return;
+  const GBlockJob<V> J = jobs[g.job];
+  mblock_run(J.B, J.b, J.diag, J.x, J.blk0 + g.tile, J.descending != 0);
+}
+
+template <class V>
 __global__ void __launch_bounds__(kBlock) k_gresidual(const GResJob<V>* __restrict__ jobs,
                                                       const GTile* __restrict__ tiles,
                                                       const int32_t* __restrict__ active) {
@@ -395,6 +611,16 @@ __global__ void __launch_bounds__(kBlock) k_gprolong(const GProlJob<V>* __restri
   const int64_t t = (int64_t)g.tile * kBlock + threadIdx.x;
   if (t >= J.n * K) return;
   mprolong_entry(J.q_col, J.q_val, J.q_cnt, (int32_t)J.n, J.xc, J.x, t);
+}
+
+template <class V>
+__global__ void __launch_bounds__(kBlock) k_gcoarse(const GCoarseJob<V>* __restrict__ jobs,
+                                                    const GTile* __restrict__ tiles,
+                                                    const int32_t* __restrict__ active) {
+  const GTile g = tiles[blockIdx.x];
+  if (!active[g.member]) return;
+  const GCoarseJob<V> J = jobs[g.job];
+  mcoarse_run(J.M, J.b, J.x, J.n, g.tile);
 }
 
 template <class V>
@@ -518,7 +744,23 @@ void mzero_columns(double* x, int64_t n, unsigned mask, hipStream_t s) {
 }
 
 template <class V>
+size_t mblock_lds(const BlockView<V>& B) {
+  if (B.nblk <= 0 || !B.hdr || !B.glist || !B.elx || !B.elv || !B.rinfo || !B.bcls) return 0;
+  const int32_t bytes = B.mlds[sizeof(V) == 8 ? 1 : 0];
+  return bytes <= kMBlockLdsMax ? (size_t)bytes : 0;
+}
+
+template <class V>
 void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool descending) {
+  if (const size_t lds = mblock_lds(v.B)) {
+    for (int k = 0; k < 4; ++k) {
+      const int bc = descending ? 3 - k : k;
+      const int32_t nb = v.B.bstart[bc + 1] - v.B.bstart[bc];
+      if (nb > 0)
+        k_mgs_block<V><<<nb, kBlkThreads, lds, s>>>(v.B, v.b, v.diag, v.x, v.B.bstart[bc], descending ? 1 : 0);
+    }
+    return;
+  }
   const int C = (int)lv.color_ptr.size() - 1;
   for (int k = 0; k < C; ++k) {
     const int c = descending ? C - 1 - k : k;
@@ -542,6 +784,13 @@ template <class V>
 void mprolong(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s) {
   k_mprolong<V><<<blocks_for((int64_t)v.n * K), kBlock, 0, s>>>(v, c.x, v.x);
 }
+
+template <class V>
+void mcoarse(const double* cinv, const LevelViewT<V>& c, hipStream_t s) {
+  k_mcoarse<V><<<mcoarse_tiles(c.n), kBlock, mcoarse_lds<V>(), s>>>(cinv, c.b, c.x, c.n);
+}
+
+int32_t mcoarse_tiles(int32_t n) { return (n + kMCoarseRows - 1) / kMCoarseRows; }
 
 void mkry_init(Batch& k, int64_t n, hipStream_t s) {
   k_mkry_init<<<blocks_for(n * K), kBlock, 0, s>>>(k.p, k.r_old, n * K, k.scal);
@@ -588,6 +837,12 @@ void gsweep(const GSweepJob<V>* jobs, const GTile* tiles, int32_t ntiles, const 
 }
 
 template <class V>
+void gblock_sweep(const GBlockJob<V>* jobs, const GTile* tiles, int32_t ntiles, size_t lds, const int32_t* active,
+                  hipStream_t s) {
+  if (ntiles > 0) k_gblock<V><<<ntiles, kBlkThreads, lds, s>>>(jobs, tiles, active);
+}
+
+template <class V>
 void gresidual(const GResJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s) {
   if (ntiles > 0) k_gresidual<V><<<ntiles, kBlock, 0, s>>>(jobs, tiles, active);
 }
@@ -600,6 +855,11 @@ void grestrict(const GRestJob<V>* jobs, const GTile* tiles, int32_t ntiles, cons
 template <class V>
 void gprolong(const GProlJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s) {
   if (ntiles > 0) k_gprolong<V><<<ntiles, kBlock, 0, s>>>(jobs, tiles, active);
+}
+
+template <class V>
+void gcoarse(const GCoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s) {
+  if (ntiles > 0) k_gcoarse<V><<<ntiles, kBlock, mcoarse_lds<V>(), s>>>(jobs, tiles, active);
 }
 
 template <class V>
@@ -648,9 +908,12 @@ void ggather_scalars(const GKryJob<V>* jobs, int32_t count, int which, uint64_t*
 
 #define GMG_INSTANTIATE_GROUPED(V)                                                                           \
   template void gsweep<V>(const GSweepJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);           \
+  template void gblock_sweep<V>(const GBlockJob<V>*, const GTile*, int32_t, size_t, const int32_t*, hipStream_t); \
+  template size_t mblock_lds<V>(const BlockView<V>&);                                                       \
   template void gresidual<V>(const GResJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
   template void grestrict<V>(const GRestJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);         \
   template void gprolong<V>(const GProlJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
+  template void gcoarse<V>(const GCoarseJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);        \
   template void gkry_init<V>(const GKryJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);          \
   template void gcycle_start<V>(const GKryJob<V>*, const GTile*, int32_t, const int32_t*, hipStream_t);       \
   template void gkry_direction<V>(const GKryJob<V>*, int32_t, const GTile*, int32_t, const int32_t*,          \
@@ -668,6 +931,7 @@ GMG_INSTANTIATE_GROUPED(float)
   template void mresidual<V>(const LevelViewT<V>&, hipStream_t);                                \
   template void mrestrict<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);          \
   template void mprolong<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);           \
+  template void mcoarse<V>(const double*, const LevelViewT<V>&, hipStream_t);                   \
   template void mkry_direction<V>(Batch&, const V*, int64_t, hipStream_t);                      \
   template void mscatter<V>(const int32_t*, const V*, int64_t, int, double*, hipStream_t);
 GMG_INSTANTIATE_MULTI(double)

@@ -61,7 +61,7 @@ __device__ __forceinline__ V row_sum_seq(const Sell<V>& A, int32_t r, const V* x
 }
 
 // The same sum over all entries of a row, for one of several interleaved
-// vectors (x's entry j at j * stride).
+// vectors (x's entry j at j * stride; in LDS or in memory).
 template <int CH, class V, class X>
 __device__ __forceinline__ V row_sum_at(const Sell<V>& A, SellRow R, X x, int32_t stride) {
   V acc = V(0);

@@ -1466,12 +1466,15 @@ __global__ void k_local_rows(const int32_t* bpos, const int32_t* blk, const int3
 
 // mx[0] = most rows, mx[1] = longest halo, mx[2] = widest ELL of any block.
 __global__ void __launch_bounds__(kBlock) k_block_maxima(const int32_t* boff, const int32_t* hoff, const int32_t* bw,
-                                                         int32_t nblk, int32_t* mx) {
-  int32_t r = 0, hl = 0, w = 0;
+                                                         int32_t nblk, int32_t C, int32_t* mx) {
+  int32_t r = 0, hl = 0, w = 0, l4 = 0, l8 = 0;
   for (int32_t b = blockIdx.x * kBlock + threadIdx.x; b < nblk; b += gridDim.x * kBlock) {
     r = max(r, boff[b + 1] - boff[b]);
     hl = max(hl, hoff[b + 1] - hoff[b]);
     w = max(w, bw[b]);
+    const int32_t rows = boff[b + 1] - boff[b], nh = hoff[b + 1] - hoff[b];
+    l4 = max(l4, mblock_layout(rows, nh, bw[b], C, 4).bytes);
+    l8 = max(l8, mblock_layout(rows, nh, bw[b], C, 8).bytes);
   }
   auto mxop = [](int32_t a, int32_t b) { return a > b ? a : b; };
   r = block_reduce(r, mxop);
@@ -1479,7 +1482,13 @@ __global__ void __launch_bounds__(kBlock) k_block_maxima(const int32_t* boff, co
   hl = block_reduce(hl, mxop);
   __syncthreads();
   w = block_reduce(w, mxop);
+  __syncthreads();
+  l4 = block_reduce(l4, mxop);
+  __syncthreads();
+  l8 = block_reduce(l8, mxop);
   if (threadIdx.x == 0) {
+    atomicMax(&mx[3], l4);
+    atomicMax(&mx[4], l8);
     atomicMax(&mx[0], r);
     atomicMax(&mx[1], hl);
     atomicMax(&mx[2], w);
@@ -1813,14 +1822,14 @@ void block_layout(Handle& h, Level& lv, int32_t C) {
   int32_t* beoff = (int32_t*)dalloc(h, (size_t)(nblk + 1) * 4);
   scan_i32(sz, beoff, nblk, s);
   tfree(s, sz);
-  int32_t* mx = (int32_t*)talloc(s, 3 * 4);
-  fill_i32(mx, 0, 3, s);
-  k_block_maxima<<<std::min(blocks_for(nblk), kReduceGrid), kBlock, 0, s>>>(boff, hoff, bw, nblk, mx);
-  int64_t v[5] = {0, 0, 0, 0, 0};
+  int32_t* mx = (int32_t*)talloc(s, 5 * 4);
+  fill_i32(mx, 0, 5, s);
+  k_block_maxima<<<std::min(blocks_for(nblk), kReduceGrid), kBlock, 0, s>>>(boff, hoff, bw, nblk, C, mx);
+  int64_t v[7] = {};
   {
-    ScalarRead rd[5] = {{beoff + nblk, 4, &v[0]}, {mx, 4, &v[1]}, {mx + 1, 4, &v[2]}, {mx + 2, 4, &v[3]},
-                        {bad, 4, &v[4]}};
-    read_scalars(h, rd, 5);
+    ScalarRead rd[7] = {{beoff + nblk, 4, &v[0]}, {mx, 4, &v[1]}, {mx + 1, 4, &v[2]}, {mx + 2, 4, &v[3]},
+                        {bad, 4, &v[4]}, {mx + 3, 4, &v[5]}, {mx + 4, 4, &v[6]}};
+    read_scalars(h, rd, 7);
   }
   tfree(s, mx);
   tfree(s, bad);
@@ -1839,6 +1848,8 @@ void block_layout(Handle& h, Level& lv, int32_t C) {
     B.rows_per_thread = maxrows <= kBlkThreads ? 1 : 2;
     B.width = maxw <= 32 ? 32 : 64;
     B.lds_bytes = (int32_t)lds;
+    B.mlds[0] = (int32_t)v[5];
+    B.mlds[1] = (int32_t)v[6];
     B.boff = boff;
     B.brows = brows;
     B.bcls = bcls;

@@ -385,8 +385,7 @@ __device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group,
       restrict_rows(r, K);
     }
   } else {
-    const V* b = J.b + vec;
-    for (int32_t i = t; i < n; i += kTailT) bc[i] = (double)b[(int64_t)i * K];
+    for (int32_t i = t; i < n; i += kTailT) bc[i] = (double)J.b[vec + (int64_t)i * K];
   }
   __syncthreads();
   // the row's products, which one lane then only has to add; columns up to a
@@ -424,17 +423,6 @@ __device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group,
 template <class V, int R>
 __global__ void GMG_COARSE_BOUNDS k_coarse(CoarseJob<V> J) {
   coarse_run<V, R>(J, (int32_t)blockIdx.x, (int32_t)blockIdx.y);
-}
-
-// The members' jobs of J.rows == R.
-template <class V, int R>
-__global__ void GMG_COARSE_BOUNDS k_gcoarse(const CoarseJob<V>* __restrict__ jobs,
-                                                    const GTile* __restrict__ tiles,
-                                                    const int32_t* __restrict__ active) {
-  const GTile g = tiles[blockIdx.x];
-  if (!active[g.member]) return;
-  const CoarseJob<V> J = jobs[g.job];
-  coarse_run<V, R>(J, g.tile, (int32_t)blockIdx.y);
 }
 
 // A_l (SELL, double) into the chunks' layout with values in V, a wavefront per
@@ -618,15 +606,6 @@ void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
 }
 
 template <class V>
-void gcoarse_fused(const CoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, int32_t rows, size_t lds,
-                   const int32_t* active, hipStream_t s) {
-  if (ntiles <= 0) return;
-  with_rows(rows, [&](auto RC) {
-    k_gcoarse<V, decltype(RC)::value><<<dim3(ntiles, kBatch), kTailT, lds, s>>>(jobs, tiles, active);
-  });
-}
-
-template <class V>
 void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s) {
   auto go = [&](auto WC) {
     k_tail_fill<V, decltype(WC)::value><<<blocks_for(nchunk, kBlock / kWave), kBlock, 0, s>>>(
@@ -646,10 +625,7 @@ void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, u
   template void tail_sweeps<V>(const TailJob<V>&, int32_t, int32_t, hipStream_t);                              \
   template void gtail_sweeps<V>(const TailJob<V>*, const int32_t*, int32_t, int32_t, int32_t, size_t, const int32_t*,   \
                                 hipStream_t);                                                                  \
-  template size_t coarse_lds<V>(const CoarseJob<V>&);                                                          \
-  template void coarse_fused<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                    \
-  template void gcoarse_fused<V>(const CoarseJob<V>*, const GTile*, int32_t, int32_t, size_t, const int32_t*,  \
-                                 hipStream_t);                                                                 \
+  template void coarse_fused<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                     \
   template void tail_fill<V>(const LevelView&, int32_t, int4*, int32_t*, uint16_t*, V*, hipStream_t);
 GMG_INSTANTIATE_TAIL(double)
 GMG_INSTANTIATE_TAIL(float)

@@ -250,3 +250,33 @@ def test_many_meshes_grouped_form():
         assert sa == sb == 0
         assert torch.equal(xa, xb)
         assert [i.iterations for i in ia] == [i.iterations for i in ib]
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("name,opt", [("ico4", dict(min_coarse_points=40, block_min_rows=20)),
+                                      ("pc4k", dict(min_coarse_points=100, block_min_rows=100)),
+                                      ("torus96", dict(min_coarse_points=200, block_min_rows=100, nu_pre=1)),
+                                      ("pc20k", dict(min_coarse_points=600, block_min_rows=600)),
+                                      ("pc100k", {})])
+def test_batched_block_sweeps(name, opt, precision):
+    """The block sweeps of 8 right-hand sides (small and large blocks, one and two
+    rows per lane group) and the batched coarsest solve, bit for bit against the
+    single-vector cycle, alone and grouped."""
+    _say(f"[gpu] batched block sweeps {name} {opt} {precision}")
+    from paper_2307_04886_amd.binding import from_problem, default_options, solve_pcg_grouped
+    prob = problem(name)
+    gpu, _ = from_problem(prob, default_options(**opt))
+    assert any(gpu.sizes(l)["blocks"] for l in range(gpu.num_levels))
+    R = np.random.default_rng(21).uniform(-1, 1, (8, prob.n))
+    Z = gpu.precondition_batched(torch.from_numpy(R).cuda(), precision=precision).cpu().numpy()
+    for q in range(8):
+        z = gpu.precondition(torch.from_numpy(R[q].copy()).cuda(), precision=precision).cpu().numpy()
+        assert_same_bits(z, Z[q], f"{name} {precision} right-hand side {q}")
+    B = torch.from_numpy(rhs_block(prob, 8)).cuda()
+    X, infos, st = gpu.solve_pcg_batched(B, precision=precision)
+    other, _ = from_problem(problem("ico4"), default_options())
+    Xs, ginfos, sts, _ = solve_pcg_grouped([other, gpu], [torch.from_numpy(rhs_block(problem("ico4"), 3)).cuda(), B],
+                                           precision=precision)
+    assert st == 0 and sts == [0, 0]
+    assert_same_bits(X.cpu().numpy(), Xs[1].cpu().numpy(), f"{name} {precision} grouped")
+    assert [i.iterations for i in infos] == [i.iterations for i in ginfos[1]]
