@@ -2,6 +2,7 @@
 // colour-sorted solve layout (SELL-64 matrix, SoA prolongation, restriction
 // rows), and the dense factorisation of the coarsest operator (Alg. 2 solves
 // the coarsest level directly).
+#include <utility>
 #include <algorithm>
 #include <cstring>
 
@@ -690,13 +691,13 @@ __global__ void k_dense_scatter(const int32_t* rp, const int32_t* col, const dou
   for (int32_t e = rp[i]; e < rp[i + 1]; ++e) D[i * n + col[e]] = val[e];
 }
 
-// Blocked right-looking dense Cholesky (32-column panels).  Entry (i, c)
-// receives its updates -L[i][j] * L[c][j] one at a time in ascending j, then
-// (below the diagonal) the division by L[c][c]: the same operations in the
-// same order as the column-by-column definition, whatever the blocking.
+// Blocked dense Cholesky (32-column panels).  Entry (i, c) receives its updates
+// -L[i][j] * L[c][j] one at a time in ascending j, then (below the diagonal)
+// the division by L[c][c]: the same operations in the same order as the
+// column-by-column definition, whatever the blocking.
 constexpr int kPanel = 32;
 
-// Lane l's value of v, for a lane index known at compile time.
+// Lane l's value of v.
 __device__ __forceinline__ double read_lane(double v, int l) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
@@ -704,102 +705,139 @@ __device__ __forceinline__ double read_lane(double v, int l) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// Factor the diagonal block of panel k0 and solve the panel rows below it.
-// The diagonal block is factored by the first wavefront, lane i holding row i
-// in registers: column c of the block is l_ic = (a_ic - sum_{m<c} l_im l_cm)
-// / l_cc (ascending m), l_cc = sqrt(a_cc - sum_{m<c} l_cm^2).
-__global__ void __launch_bounds__(256) k_chol_panel(double* D, int64_t n, int64_t k0, int32_t* flags) {
-  __shared__ double T[kPanel][kPanel + 1];
-  __shared__ int bad;
+// One step of the factorisation, in one launch: the updates of panel j0 = k0 - 32
+// (none at k0 = 0) to everything right of it, and the factorisation of panel k0.
+// D holds the matrix with the updates of the panels before j0; the factor goes
+// to L and, transposed, to U, so that no workgroup reads what another writes.
+//
+// The first `groups` workgroups each take 32 of the rows below the diagonal
+// block of panel k0, and that block as well: all of them factor it alike, in
+// wavefronts whose lanes 0-31 hold the rows of the block and lanes 32-63 the
+// rows below.  Eight columns at a time: the first wavefront runs their chain of
+// square root, division and first update (206 cycles a column), then the eight
+// wavefronts update the columns to the right, a wavefront getting one double
+// precision operation in 8 cycles.  The other workgroups update the tiles right
+// of panel k0.  194 rows: 12.4 us a panel, of which the columns 8 us (the block
+// in one wavefront, then the rows below it in registers, then the tiles in a
+// second launch: 25 + 4.7 us).
+constexpr int kCholT = 512;
+__global__ void __launch_bounds__(kCholT) k_chol_step(double* __restrict__ D, int32_t n, int32_t k0, int32_t groups,
+                                                      double* __restrict__ L, double* __restrict__ U,
+                                                      int32_t* flags) {
+  __shared__ double P[2 * kPanel][kPanel + 1];      // panel j0: rows of the group (or of the tile's two ranges)
   const int tid = threadIdx.x;
-  const int kb = (int)(n - k0 < kPanel ? n - k0 : kPanel);
-  if (tid < kWave) {
-    const int i = tid;
-    double r[kPanel];
+  const int32_t j0 = k0 - kPanel, kb = min(n - k0, kPanel);
+  const bool first = k0 == 0;
+  constexpr int kRows = kCholT / kPanel, kPer = 2 * kPanel / kRows, kSub = 8;
+  const int cc = tid % kPanel, r0 = tid / kPanel;
+  if ((int32_t)blockIdx.x < groups) {
+    __shared__ double R[2 * kPanel][kPanel + 1];
+    const int32_t below = k0 + kPanel + (int32_t)blockIdx.x * kPanel;   // first row below of this group
+    auto row_of = [&](int r) { return r < kPanel ? k0 + r : below + r - kPanel; };
+    double pv[kPer], dv[kPer];                     // all loads in flight together
 #pragma unroll
-    for (int c = 0; c < kPanel; ++c) r[c] = (i < kb && c <= i) ? D[(k0 + i) * n + k0 + c] : 0.0;
-    bool ok = true;
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t i = min(row_of(r0 + u * kRows), n - 1);
+      pv[u] = first ? 0.0 : L[i * n + j0 + cc];
+      dv[u] = D[i * n + min(k0 + cc, n - 1)];
+    }
 #pragma unroll
-    for (int c = 0; c < kPanel; ++c) {
-      if (c < kb) {
-        double t = r[c];
+    for (int u = 0; u < kPer; ++u) {
+      const int r = r0 + u * kRows;
+      P[r][cc] = row_of(r) < n ? pv[u] : 0.0;
+      const bool in = row_of(r) < n && cc < kb && (r >= kPanel || cc <= r);
+      R[r][cc] = in ? dv[u] : (r == cc ? 1.0 : 0.0);   // past the matrix: the identity's columns
+    }
+    __syncthreads();
+    // the updates of panel j0, four columns a wavefront
+    const int lane = tid % kWave, w = tid / kWave;
+    if (!first) {
+      double a[kSub / 2];
 #pragma unroll
-        for (int m = 0; m < c; ++m) t = t - r[m] * read_lane(r[m], c);
-        const double dc = read_lane(t, c);
-        ok = ok && dc > 0.0;
-        const double d = ok ? sqrt(dc) : 1.0;
-        if (i == c) r[c] = d;
-        else if (i > c) r[c] = t / d;
+      for (int u = 0; u < kSub / 2; ++u) a[u] = R[lane][w * (kSub / 2) + u];
+#pragma unroll 4
+      for (int j = 0; j < kPanel; ++j) {
+        const double l = P[lane][j];
+#pragma unroll
+        for (int u = 0; u < kSub / 2; ++u) a[u] = a[u] - l * P[w * (kSub / 2) + u][j];
       }
-      __builtin_amdgcn_sched_barrier(0);   // one column at a time: bounds the live registers
+#pragma unroll
+      for (int u = 0; u < kSub / 2; ++u) R[lane][w * (kSub / 2) + u] = a[u];
+      __syncthreads();
     }
-    if (i < kb) {
+    for (int g = 0; g < kb; g += kSub) {
+      if (w == 0) {
+        double r[kSub];
+        bool ok = true;
 #pragma unroll
-      for (int c = 0; c < kPanel; ++c)
-        if (c <= i) T[i][c] = r[c];
-    }
-    if (ok && i < kb) {
+        for (int u = 0; u < kSub; ++u) r[u] = R[lane][g + u];
 #pragma unroll
-      for (int c = 0; c < kPanel; ++c)
-        if (c <= i) D[(k0 + i) * n + k0 + c] = r[c];
-    }
-    if (tid == 0) {
-      bad = ok ? 0 : 1;
-      if (!ok) atomicOr(flags, F_NOT_SPD);
-    }
-  }
-  __syncthreads();
-  if (bad) return;
-  // panel rows: l_ij = (a_ij - sum_{k0 <= m < j} l_im l_jm) / l_jj, ascending j
-  for (int64_t i = k0 + kb + tid; i < n; i += blockDim.x) {
-    double a[kPanel];
+        for (int u = 0; u < kSub; ++u) {
+          const double dc = read_lane(r[u], g + u);
+          ok = ok && dc > 0.0;
+          const double d = ok ? sqrt(dc) : 1.0;
+          r[u] = lane == g + u ? d : r[u] / d;
 #pragma unroll
-    for (int j = 0; j < kPanel; ++j) a[j] = j < kb ? D[i * n + k0 + j] : 0.0;
+          for (int m = u + 1; m < kSub; ++m) r[m] = r[m] - r[u] * read_lane(r[u], g + m);
+        }
 #pragma unroll
-    for (int j = 0; j < kPanel; ++j) {
-      if (j < kb) {
-        double t = a[j];
-#pragma unroll
-        for (int m = 0; m < j; ++m) t = t - a[m] * T[j][m];
-        a[j] = t / T[j][j];
+        for (int u = 0; u < kSub; ++u) R[lane][g + u] = r[u];
+        if (!ok && lane == 0 && blockIdx.x == 0) atomicOr(flags, F_NOT_SPD);
       }
-      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
+      double l[kSub];
+#pragma unroll
+      for (int u = 0; u < kSub; ++u) l[u] = R[lane][g + u];
+#pragma unroll
+      for (int t = 0; t < kPanel / kSub - 1; ++t) {
+        const int c = g + kSub + w + t * (kCholT / kWave);
+        if (c < kPanel) {
+          double a = R[lane][c];
+#pragma unroll
+          for (int u = 0; u < kSub; ++u) a = a - l[u] * R[c][g + u];
+          R[lane][c] = a;
+        }
+      }
+      __syncthreads();
     }
 #pragma unroll
-    for (int j = 0; j < kPanel; ++j)
-      if (j < kb) D[i * n + k0 + j] = a[j];
+    for (int u = 0; u < kPer; ++u) {
+      const int r = r0 + u * kRows, i = row_of(r);
+      if (i < n && cc < kb && (r >= kPanel || (blockIdx.x == 0 && cc <= r))) L[(int64_t)i * n + k0 + cc] = R[r][cc];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int c = w + u * (kCholT / kWave), i = row_of(lane);
+      if (i < n && c < kb && (lane >= kPanel || (blockIdx.x == 0 && c <= lane))) U[(int64_t)(k0 + c) * n + i] = R[lane][c];
+    }
+    return;
   }
-}
-
-// Trailing update of the lower triangle below panel k0: one 32x32 tile per
-// workgroup, a_ic <- a_ic - l_ij l_cj for the panel columns j in ascending order.
-__global__ void __launch_bounds__(1024) k_chol_update(double* D, int64_t n, int64_t k0, int kb) {
-  __shared__ double LI[kPanel][kPanel + 1];
-  __shared__ double LC[kPanel][kPanel + 1];
-  const int64_t base = k0 + kb;
-  const int64_t I = blockIdx.y, C = blockIdx.x;
-  if (C > I) return;
-  const int ti = threadIdx.x / kPanel, tc = threadIdx.x % kPanel;
-  const int64_t gi = base + I * kPanel + ti, gc = base + C * kPanel + ti;
-  LI[ti][tc] = (gi < n && tc < kb) ? D[gi * n + k0 + tc] : 0.0;
-  LC[ti][tc] = (gc < n && tc < kb) ? D[gc * n + k0 + tc] : 0.0;
+  // a_ic <- a_ic - l_ij l_cj for the columns j of panel j0: tile (I, C) of the lower triangle
+  int32_t t = (int32_t)blockIdx.x - groups, I = 0;
+  while (t > I) t -= ++I;
+  const int32_t ri = k0 + kPanel + I * kPanel, rc = k0 + kPanel + t * kPanel;
+  double pv[kPer], a[kPer / 2];
+  const int32_t c = rc + cc;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int r = r0 + u * kRows;
+    pv[u] = L[(int64_t)min(r < kPanel ? ri + r : rc + r - kPanel, n - 1) * n + j0 + cc];
+    if (u < kPer / 2) a[u] = D[(int64_t)min(ri + r, n - 1) * n + min(c, n - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) P[r0 + u * kRows][cc] = pv[u];
   __syncthreads();
-  const int64_t i = base + I * kPanel + ti, c = base + C * kPanel + tc;
-  if (i < n && c <= i) {
-    double a = D[i * n + c];
-    for (int j = 0; j < kb; ++j) a = a - LI[ti][j] * LC[tc][j];
-    D[i * n + c] = a;
+#pragma unroll 4
+  for (int j = 0; j < kPanel; ++j) {
+    const double l = P[kPanel + cc][j];
+#pragma unroll
+    for (int u = 0; u < kPer / 2; ++u) a[u] = a[u] - P[r0 + u * kRows][j] * l;
   }
-}
-
-// Lower factor L (zeros above the diagonal) and its transpose U.
-__global__ void k_split_factor(const double* D, int64_t n, double* L, double* U) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * n) return;
-  int64_t i = idx / n, k = idx % n;
-  double v = k <= i ? D[i * n + k] : 0.0;
-  L[idx] = v;
-  U[k * n + i] = v;
+#pragma unroll
+  for (int u = 0; u < kPer / 2; ++u) {
+    const int32_t i = ri + r0 + u * kRows;
+    if (i < n && c <= i) D[(int64_t)i * n + c] = a[u];
+  }
 }
 
 // Column c of the coarsest inverse, A^-1 e_c, by substitution with the
@@ -812,81 +850,91 @@ __global__ void k_split_factor(const double* D, int64_t n, double* L, double* U)
 // product with y_k = +0), so the forward pass starts at row c.
 //
 // One wavefront per column: lane l holds rows l, l + 64, ... (S slots) in
-// registers and the pivot row's value is read across lanes; the factor
-// entries of the next D steps are loaded ahead (phase k mod D of a ring).
+// registers, with their pivots, and the pivot row's value is read across lanes;
+// the factor entries of the next D steps are loaded ahead (phase k mod D of a
+// ring).  What bounds a column is its chain, a division, a product and a
+// difference per step (130 cycles), as long as no step waits for a load: the
+// loads are therefore issued without conditions, past the last row those of the
+// last row again (loads under conditions had the compiler wait for the newest
+// one, and a pivot loaded as a scalar for all: 450 cycles a step; 194 rows: 88 us,
+// now 43; 513-768 rows: 484, now 237; 1000 rows: 907, now 428).
+template <class F, int... Q>
+__device__ __forceinline__ void each_slot_of(F&& f, std::integer_sequence<int, Q...>) {
+  (f(std::integral_constant<int, Q>{}), ...);
+}
+template <int S, class F>
+__device__ __forceinline__ void each_slot(F&& f) {
+  each_slot_of(f, std::make_integer_sequence<int, S>{});
+}
+
 template <int S, int D>
 __global__ void __launch_bounds__(kWave) k_coarse_inverse(const double* __restrict__ L,
                                                          const double* __restrict__ U, int32_t n,
                                                          double* __restrict__ inv) {
   const int32_t c = blockIdx.x;
   const int lane = threadIdx.x;
-  double s[S];
-#pragma unroll
-  for (int q = 0; q < S; ++q) s[q] = q * kWave + lane == c ? 1.0 : 0.0;
-  double f[D][S], d[D];                       // ring: factor entries and pivot of step k at phase k mod D
-  // forward: step k uses column k of L (row k of U) for rows i > k
-  auto load_fwd = [&](int j, int32_t k) {
-    if (k >= n) return;
-    d[j] = L[(int64_t)k * n + k];
-#pragma unroll
-    for (int q = 0; q < S; ++q)
-      if (q * kWave + kWave - 1 > k) f[j][q] = U[(int64_t)k * n + min(q * kWave + lane, n - 1)];
-  };
-#pragma unroll
-  for (int j = 0; j < D; ++j) load_fwd(j, c + ((j - c) % D + D) % D);
+  double s[S], d[S], f[D][S];                 // f: factor entries of step k at phase k mod D
+  int32_t at[S];                              // the slots' rows (past the end: the last row)
 #pragma unroll
   for (int q = 0; q < S; ++q) {
-    const int32_t k_lo = max(c, q * kWave), k_hi = min(n, (q + 1) * kWave);
-    for (int32_t k0 = k_lo - k_lo % D; k0 < k_hi; k0 += D) {
+    at[q] = min(q * kWave + lane, n - 1);
+    s[q] = q * kWave + lane == c ? 1.0 : 0.0;
+    d[q] = L[(int64_t)at[q] * n + at[q]];
+  }
+  // forward: step k uses column k of L (row k of U) for rows i > k
+  const int32_t k_first = c - c % D;
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+#pragma unroll
+    for (int q = 0; q < S; ++q) f[j][q] = U[(int64_t)min(k_first + j, n - 1) * n + at[q]];
+  each_slot<S>([&](auto Q) {
+    constexpr int q = Q;
+    const int32_t k_hi = min(n, (q + 1) * kWave);
+    for (int32_t k0 = max(k_first, q * kWave); k0 < k_hi; k0 += D) {
 #pragma unroll
       for (int j = 0; j < D; ++j) {
         const int32_t k = k0 + j;
-        if (k >= k_lo && k < k_hi) {
-          const double y = read_lane(s[q], k & (kWave - 1)) / d[j];
-          if (lane == (k & (kWave - 1))) s[q] = y;
+        if (k >= c && k < n) {
+          const double y = read_lane(s[q], k & (kWave - 1)) / read_lane(d[q], k & (kWave - 1));
+          const double t = s[q] - f[j][q] * y;
+          const int32_t i = q * kWave + lane;
+          s[q] = i > k ? t : (i == k ? y : s[q]);
 #pragma unroll
-          for (int q2 = q; q2 < S; ++q2) {
-            const int32_t i = q2 * kWave + lane;
-            if (i > k && i < n) s[q2] = s[q2] - f[j][q2] * y;
-          }
-          load_fwd(j, k + D);
+          for (int q2 = q + 1; q2 < S; ++q2) s[q2] = s[q2] - f[j][q2] * y;
         }
+        const double* __restrict__ row = U + (int64_t)min(k + D, n - 1) * n;
+#pragma unroll
+        for (int q2 = q; q2 < S; ++q2) f[j][q2] = row[at[q2]];
       }
     }
-  }
-  // back: step i uses row i of L for rows r < i
-  auto load_bwd = [&](int j, int32_t i) {
-    if (i < 0) return;
-    d[j] = L[(int64_t)i * n + i];
+  });
+  // back: step i uses row i of L for rows r < i (rows past the end hold no row's value)
+  const int32_t i_first = n - 1 + (D - 1 - (n - 1) % D);
 #pragma unroll
-    for (int q = 0; q < S; ++q)
-      if (q * kWave < i) f[j][q] = L[(int64_t)i * n + min(q * kWave + lane, n - 1)];
-  };
+  for (int j = 0; j < D; ++j)
 #pragma unroll
-  for (int j = 0; j < D; ++j) load_bwd(j, (n - 1) - (((n - 1 - j) % D) + D) % D);
-#pragma unroll
-  for (int q = S - 1; q >= 0; --q) {
-    const int32_t i_hi = min(n, (q + 1) * kWave) - 1, i_lo = q * kWave;
-    if (i_hi < i_lo) continue;
+    for (int q = 0; q < S; ++q) f[j][q] = L[(int64_t)min(i_first - (D - 1) + j, n - 1) * n + at[q]];
+  each_slot<S>([&](auto Q) {
+    constexpr int q = S - 1 - Q;
     // groups of D steps aligned to multiples of D, top step i0 first
-    for (int32_t i0 = i_hi + (D - 1 - i_hi % D); i0 >= i_lo; i0 -= D) {
+    for (int32_t i0 = min(i_first, (q + 1) * kWave - 1); i0 >= q * kWave; i0 -= D) {
 #pragma unroll
-      for (int jj = D - 1; jj >= 0; --jj) {
-        const int32_t i = i0 - (D - 1) + jj;        // descending within the group
-        const int j = jj;
-        if (i >= i_lo && i <= i_hi) {
-          const double x = read_lane(s[q], i & (kWave - 1)) / d[j];
-          if (lane == (i & (kWave - 1))) s[q] = x;
+      for (int j = D - 1; j >= 0; --j) {
+        const int32_t i = i0 - (D - 1) + j;
+        if (i < n) {
+          const double x = read_lane(s[q], i & (kWave - 1)) / read_lane(d[q], i & (kWave - 1));
+          const double t = s[q] - f[j][q] * x;
+          const int32_t r = q * kWave + lane;
+          s[q] = r < i ? t : (r == i ? x : s[q]);
 #pragma unroll
-          for (int q2 = 0; q2 <= q; ++q2) {
-            const int32_t r = q2 * kWave + lane;
-            if (r < i) s[q2] = s[q2] - f[j][q2] * x;
-          }
-          load_bwd(j, i - D);
+          for (int q2 = 0; q2 < q; ++q2) s[q2] = s[q2] - f[j][q2] * x;
         }
+        const double* __restrict__ row = L + (int64_t)max(i - D, 0) * n;
+#pragma unroll
+        for (int q2 = 0; q2 <= q; ++q2) f[j][q2] = row[at[q2]];
       }
     }
-  }
+  });
   const int32_t ld = (int32_t)inv_ld(n);
 #pragma unroll
   for (int q = 0; q < S; ++q) {
@@ -2063,10 +2111,11 @@ void solve_layout(Handle& h, Level& lv, const Level* nx, const int32_t* t_rp, co
   tfree(s, off);
 }
 
-// Slots per lane of the register form, with the depth of its load ring.
+// Slots per lane of the register form, with the depth of its load ring (as deep as
+// 512 registers hold: a wavefront has a SIMD to itself up to 1024 columns).
 template <int S>
 void launch_inverse(const double* L, const double* U, int32_t n, double* inv, hipStream_t s) {
-  constexpr int D = S <= 4 ? 8 : (S <= 8 ? 4 : 2);
+  constexpr int D = S <= 8 ? 8 : 4;
   k_coarse_inverse<S, D><<<n, kWave, 0, s>>>(L, U, n, inv);
 }
 
@@ -2095,18 +2144,16 @@ void coarse_factor(Handle& h, Level& lv) {
   double* U = (double*)talloc(s, (size_t)n * n * 8);
   check_hip(hipMemsetAsync(D, 0, (size_t)n * n * 8, s), "memset");
   k_dense_scatter<<<blocks_for(n), kBlock, 0, s>>>(lv.arp, lv.acol, lv.aval, n, D);
-  for (int64_t k0 = 0; k0 < n; k0 += kPanel) {
-    const int kb = (int)std::min<int64_t>(kPanel, n - k0);
-    k_chol_panel<<<1, 256, 0, s>>>(D, n, k0, h.flags);
-    const int64_t m = n - k0 - kb;
-    if (m > 0) {
-      const int t = (int)((m + kPanel - 1) / kPanel);
-      k_chol_update<<<dim3(t, t), 1024, 0, s>>>(D, n, k0, kb);
-    }
+  if (!h.chol) {                              // zeros above the diagonal
+    h.chol = (double*)dalloc(h, (size_t)n * n * 8);
+    check_hip(hipMemsetAsync(h.chol, 0, (size_t)n * n * 8, s), "memset");
   }
-  if (!h.chol) h.chol = (double*)dalloc(h, (size_t)n * n * 8);
   if (!h.cinv) h.cinv = (double*)dalloc(h, (size_t)n * inv_ld(n) * 8);
-  k_split_factor<<<blocks_for(n * n), kBlock, 0, s>>>(D, n, h.chol, U);
+  for (int64_t k0 = 0; k0 < n; k0 += kPanel) {
+    const int64_t below = std::max<int64_t>(0, (n - k0 - 1) / kPanel);   // 32-row groups below the diagonal block
+    const int64_t groups = std::max<int64_t>(1, below), tiles = k0 > 0 ? below * (below + 1) / 2 : 0;
+    k_chol_step<<<(int)(groups + tiles), kCholT, 0, s>>>(D, (int32_t)n, (int32_t)k0, (int32_t)groups, h.chol, U, h.flags);
+  }
   coarse_inverse(h.chol, U, n, h.cinv, s);
   h.ncoarse = n;
   check_flags(h, "coarsest factorisation");
