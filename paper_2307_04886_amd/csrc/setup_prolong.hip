@@ -387,15 +387,16 @@ __device__ inline int wave_incl_scan(int v) {
   return v;
 }
 
+// Slot of J in the table, entered if it is not there; -1: the table is full.
 template <int HS>
-__device__ inline bool hash_insert(int32_t* keys, int32_t J) {
+__device__ inline int32_t hash_insert(int32_t* keys, int32_t J) {
   uint32_t h = ((uint32_t)J * 2654435761u) & (HS - 1);
   for (int probe = 0; probe < HS; ++probe) {
     int32_t old = atomicCAS(&keys[h], -1, J);
-    if (old == -1 || old == J) return true;
+    if (old == -1 || old == J) return (int32_t)h;
     h = (h + 1) & (HS - 1);
   }
-  return false;
+  return -1;
 }
 
 struct PairChunk {
@@ -472,7 +473,7 @@ __global__ void __launch_bounds__(kWave) k_galerkin_count(const int32_t* trp, co
     for (int u = 0; u < kFastSub; ++u)
 #pragma unroll
       for (int t = 0; t < 3; ++t)
-        if (t < fc[u]) ok &= hash_insert<HS>(keys, fJ[u][t]);
+        if (t < fc[u]) ok &= hash_insert<HS>(keys, fJ[u][t]) >= 0;
     __syncthreads();
   } else {
     for (int32_t q0 = qb; q0 < qe; q0 += kWave) {
@@ -485,7 +486,7 @@ __global__ void __launch_bounds__(kWave) k_galerkin_count(const int32_t* trp, co
           locate_pair(pc, p, src, e);
           const int32_t j = acol[e];
           const int c = pcnt[j];
-          for (int t = 0; t < c; ++t) ok &= hash_insert<HS>(keys, pcol[3 * j + t]);
+          for (int t = 0; t < c; ++t) ok &= hash_insert<HS>(keys, pcol[3 * j + t]) >= 0;
         }
       }
       __syncthreads();
@@ -513,15 +514,14 @@ __global__ void __launch_bounds__(kWave) k_galerkin_fill(const int32_t* trp, con
   // or, with crp null, to I * kOut of padded rows with its length in rowcnt[I];
   // a row with more than kOut columns then sets *unfit and is left out.
   constexpr int kOut = HS * 3 / 4;     // distinct columns of a row
-  constexpr int kFastSub = 4;          // pairs per lane of the one-chunk form
+  constexpr int kSub = 4;              // pairs of a lane whose loads are in flight together
   constexpr int kPer = (kOut + kWave - 1) / kWave;   // output columns per lane
   __shared__ int32_t keys[HS];
   __shared__ int32_t rank_of[HS];      // hash slot -> position of its column in the sorted row
   __shared__ int32_t sorted[kOut];
-  __shared__ double accum[kOut];
   __shared__ unsigned long long hits[kOut];   // per output column: the pairs of the chunk that add to it
-  __shared__ int32_t tR[3 * kWave];    // per pair of the chunk: output position of each term (-1: none)
-  __shared__ double tV[3 * kWave];     // and its value
+  __shared__ int32_t first[kOut];      // the column's first term in `terms`
+  __shared__ double terms[3 * kWave];  // the chunk's terms, column by column in pair order
   __shared__ PairChunk pc;
   __shared__ int32_t nlist;
   const int32_t I = (int32_t)xcd_block();        // neighbouring rows share an XCD
@@ -531,35 +531,45 @@ __global__ void __launch_bounds__(kWave) k_galerkin_fill(const int32_t* trp, con
   for (int s = lane; s < HS; s += kWave) keys[s] = -1;
   if (lane == 0) nlist = 0;
   __syncthreads();
-  // Rows with one chunk of P^T entries and at most kFastSub * 64 pairs keep
-  // the chunk and each lane's pairs (pair lane + 64 s) in registers for both
-  // passes, with every gather of a pass issued together; other rows reload
-  // them chunk by chunk.
+  // Rows with one chunk of P^T entries take their pairs kSub * 64 at a time (pair
+  // p0 + lane + 64 u), with every gather of a pass issued together; a row of one
+  // such batch keeps it in registers for both passes.  Other rows reload their
+  // pairs chunk by chunk.
   const int32_t qb = trp[I], qe = trp[I + 1];
-  int tot = qe - qb <= kWave ? load_pairs(qb, qe, tcol, tval, arp, pc) : kFastSub * kWave + 1;
-  const bool fast = tot <= kFastSub * kWave;                        // uniform over the wavefront
-  int fsrc[kFastSub], fc[kFastSub];
-  int32_t fe[kFastSub], fj[kFastSub], fJ[kFastSub][3];
-  if (fast) {
+  const bool one = qe - qb <= kWave;                                // uniform over the wavefront
+  const int tot = one ? load_pairs(qb, qe, tcol, tval, arp, pc) : 0;
+  int fsrc[kSub], fc[kSub];
+  int32_t fe[kSub], fj[kSub], fs[kSub][3];                          // fs: columns, then their hash slots
+  auto load_batch = [&](int p0) {
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u) {
+    for (int u = 0; u < kSub; ++u) {
       fsrc[u] = 0;
       fe[u] = 0;
-      if (lane + u * kWave < tot) locate_pair(pc, lane + u * kWave, fsrc[u], fe[u]);
+      if (p0 + lane + u * kWave < tot) locate_pair(pc, p0 + lane + u * kWave, fsrc[u], fe[u]);
     }
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u) fj[u] = lane + u * kWave < tot ? acol[fe[u]] : 0;
+    for (int u = 0; u < kSub; ++u) fj[u] = p0 + lane + u * kWave < tot ? acol[fe[u]] : 0;
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u) {
-      fc[u] = lane + u * kWave < tot ? pcnt[fj[u]] : 0;
+    for (int u = 0; u < kSub; ++u) {
+      fc[u] = p0 + lane + u * kWave < tot ? pcnt[fj[u]] : 0;
 #pragma unroll
-      for (int t = 0; t < 3; ++t) fJ[u][t] = pcol[3 * fj[u] + t];
+      for (int t = 0; t < 3; ++t) fs[u][t] = pcol[3 * fj[u] + t];
     }
+  };
+  auto find = [&](int32_t J) {
+    uint32_t h = ((uint32_t)J * 2654435761u) & (HS - 1);
+    while (keys[h] != J) h = (h + 1) & (HS - 1);
+    return (int32_t)h;
+  };
+  if (one) {
+    for (int p0 = 0; p0 < tot; p0 += kSub * kWave) {
+      load_batch(p0);
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u)
+      for (int u = 0; u < kSub; ++u)
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
-        if (t < fc[u]) hash_insert<HS>(keys, fJ[u][t]);
+        for (int t = 0; t < 3; ++t)
+          if (t < fc[u]) fs[u][t] = hash_insert<HS>(keys, fs[u][t]);
+    }
     __syncthreads();
   } else {
     for (int32_t q0 = qb; q0 < qe; q0 += kWave) {
@@ -609,67 +619,98 @@ __global__ void __launch_bounds__(kWave) k_galerkin_fill(const int32_t* trp, con
   __syncthreads();
 #pragma unroll
   for (int g = 0; g < kPer; ++g)
-    if (lane + g * kWave < k) {
-      sorted[rank_of[myslot[g]]] = mykey[g];
-      accum[rank_of[myslot[g]]] = 0.0;
-    }
+    if (lane + g * kWave < k) sorted[rank_of[myslot[g]]] = mykey[g];
   __syncthreads();
   // Numeric pass, 64 (i, j) pairs at a time in definition order.  Each pair
   // adds at most one term to an output column (the columns of a row of P are
-  // distinct), so the owner of column o adds the terms of the pairs flagged in
-  // hits[o] in ascending pair order: every entry is summed in the order of the
-  // definition.
-  // The terms of one 64-pair chunk of the one-chunk form: pair lane has c
-  // terms (P row of j, t1 = P[i,I] A[i,j] times P[j,J_t]); the owner of each
-  // output column adds them in pair order.  (The general form below does the
-  // same with its loads inline.)
-  auto add_chunk = [&](int c, const int32_t* J, const double* v) {
-    for (int o = lane; o < k; o += kWave) hits[o] = 0ull;
+  // distinct), so with the pairs flagged in hits[o] the term of pair `lane` is
+  // the (flags below lane)-th of column o: the chunk's terms are laid out column
+  // by column, and the owner of a column adds its own from there, in ascending
+  // pair order: every entry is summed in the order of the definition.  (Most pairs
+  // add to the row's own column; its owner finding each of them through the flags
+  // took 270 cycles a term, and 17,000 of a chunk's 19,000: 10,242 points 92 us a
+  // level, now 41; 65,536: 122, now 57; 1,048,576: 328, now 224.)
+  // Pair lane of a chunk has c terms v (t1 = P[i,I] A[i,j] times P[j,J_t]), to the
+  // columns J in the hash slots `slot`.
+  double acc[kPer];
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      int32_t r = -1;
-      if (t < c) {
-        uint32_t h = ((uint32_t)J[t] * 2654435761u) & (HS - 1);
-        while (keys[h] != J[t]) h = (h + 1) & (HS - 1);
-        r = rank_of[h];
-      }
-      tR[3 * lane + t] = r;
-      tV[3 * lane + t] = t < c ? v[t] : 0.0;
+  for (int g = 0; g < kPer; ++g) acc[g] = 0.0;
+  auto add_chunk = [&](int c, const int32_t* slot, const double* v) {
+    for (int o = lane; o < k; o += kWave) hits[o] = 0ull;
+    int32_t r[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) r[t] = t < c ? rank_of[slot[t]] : 0;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < c) atomicOr(&hits[r[t]], 1ull << lane);
+    __syncthreads();
+    int32_t at = 0;
+#pragma unroll
+    for (int g = 0; g < kPer; ++g) {
+      if (g * kWave >= k) break;                                     // uniform
+      const int o = lane + g * kWave;
+      const int32_t n = o < k ? __popcll(hits[o]) : 0;
+      const int32_t incl = wave_incl_scan(n);
+      if (o < k) first[o] = at + incl - n;
+      at += __shfl(incl, kWave - 1, kWave);
     }
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < 3; ++t)
-      if (t < c) atomicOr(&hits[tR[3 * lane + t]], 1ull << lane);
+      if (t < c) terms[first[r[t]] + __popcll(hits[r[t]] & ((1ull << lane) - 1ull))] = v[t];
     __syncthreads();
-    for (int o = lane; o < k; o += kWave) {
-      unsigned long long m = hits[o];
-      double acc = accum[o];
-      while (m) {
-        const int q = __builtin_ctzll(m);
-        m &= m - 1;
-        const int t = tR[3 * q] == o ? 0 : (tR[3 * q + 1] == o ? 1 : 2);
-        acc = acc + tV[3 * q + t];
+#pragma unroll
+    for (int g = 0; g < kPer; ++g) {
+      const int o = lane + g * kWave;
+      if (o >= k) break;
+      const int32_t n = __popcll(hits[o]), b = first[o];
+      double x[8], y[8];                                             // the next eight in flight beside the sum
+      auto read = [&](double* d, int32_t q) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) d[u] = terms[min(b + q + u, 3 * kWave - 1)];
+      };
+      read(x, 0);
+      int32_t q = 0;
+      for (; q + 8 <= n; q += 8) {
+        read(y, q + 8);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[g] = acc[g] + x[u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = y[u];
       }
-      accum[o] = acc;
+#pragma unroll
+      for (int u = 0; u < 7; ++u)
+        if (q + u < n) acc[g] = acc[g] + x[u];
     }
     __syncthreads();
   };
-  if (fast) {
-    double fa[kFastSub], fp[kFastSub][3];
+  if (one) {
+    for (int p0 = 0; p0 < tot; p0 += kSub * kWave) {
+      if (tot > kSub * kWave) {
+        load_batch(p0);
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u) {
-      fa[u] = aval[fe[u]];
+        for (int u = 0; u < kSub; ++u)
 #pragma unroll
-      for (int t = 0; t < 3; ++t) fp[u][t] = pval[3 * fj[u] + t];
-    }
+          for (int t = 0; t < 3; ++t)
+            if (t < fc[u]) fs[u][t] = find(fs[u][t]);
+      }
+      double fa[kSub], fp[kSub][3];
 #pragma unroll
-    for (int u = 0; u < kFastSub; ++u) {
-      if (u * kWave >= tot) break;                                   // uniform
-      const double t1 = pc.piI[fsrc[u]] * fa[u];
-      double v[3];
+      for (int u = 0; u < kSub; ++u) {
+        fa[u] = aval[fe[u]];
 #pragma unroll
-      for (int t = 0; t < 3; ++t) v[t] = t1 * fp[u][t];
-      add_chunk(fc[u], fJ[u], v);
+        for (int t = 0; t < 3; ++t) fp[u][t] = pval[3 * fj[u] + t];
+      }
+#pragma unroll
+      for (int u = 0; u < kSub; ++u) {
+        if (p0 + u * kWave >= tot) break;                            // uniform
+        const double t1 = pc.piI[fsrc[u]] * fa[u];
+        double v[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) v[t] = t1 * fp[u][t];
+        add_chunk(fc[u], fs[u], v);
+      }
     }
   } else {
     for (int32_t q0 = qb; q0 < qe; q0 += kWave) {
@@ -688,48 +729,28 @@ __global__ void __launch_bounds__(kWave) k_galerkin_fill(const int32_t* trp, con
           c = pcnt[j];
           t1 = pc.piI[src] * aval[e];
         }
-        for (int o = lane; o < k; o += kWave) hits[o] = 0ull;
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-          int32_t r = -1;
-          double v = 0.0;
-          if (t < c) {
-            const int32_t J = pcol[3 * j + t];
-            uint32_t h = ((uint32_t)J * 2654435761u) & (HS - 1);
-            while (keys[h] != J) h = (h + 1) & (HS - 1);
-            r = rank_of[h];
-            v = t1 * pval[3 * j + t];
-          }
-          tR[3 * lane + t] = r;
-          tV[3 * lane + t] = v;
-        }
-        __syncthreads();
+        int32_t J[3];
+        double v[3];
 #pragma unroll
         for (int t = 0; t < 3; ++t)
-          if (t < c) atomicOr(&hits[tR[3 * lane + t]], 1ull << lane);
-        __syncthreads();
-        for (int o = lane; o < k; o += kWave) {
-          unsigned long long m = hits[o];
-          double acc = accum[o];
-          while (m) {
-            const int q = __builtin_ctzll(m);
-            m &= m - 1;
-            const int t = tR[3 * q] == o ? 0 : (tR[3 * q + 1] == o ? 1 : 2);
-            acc = acc + tV[3 * q + t];
+          if (t < c) {
+            J[t] = find(pcol[3 * j + t]);
+            v[t] = t1 * pval[3 * j + t];
           }
-          accum[o] = acc;
-        }
-        __syncthreads();
+        add_chunk(c, J, v);
       }
     }
   }
   const int64_t out = crp ? (int64_t)crp[I] : (int64_t)I * kOut;
   if (rowcnt && lane == 0) rowcnt[I] = k;
   bool diag_ok = false;
-  for (int o = lane; o < k; o += kWave) {
+#pragma unroll
+  for (int g = 0; g < kPer; ++g) {
+    const int o = lane + g * kWave;
+    if (o >= k) break;
     ccol[out + o] = sorted[o];
-    cval[out + o] = accum[o];
-    if (sorted[o] == I && accum[o] > 0.0) diag_ok = true;
+    cval[out + o] = acc[g];
+    if (sorted[o] == I && acc[g] > 0.0) diag_ok = true;
   }
   // a missing or non-positive diagonal makes Gauss-Seidel divide by zero
   unsigned long long bal = __ballot(diag_ok);

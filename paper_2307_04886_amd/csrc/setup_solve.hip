@@ -1454,11 +1454,14 @@ __global__ void k_block_entries(const int32_t* rp, const int32_t* perm, const in
   }
 }
 
-// The block ELL, one workgroup per block (its halo in LDS): entry t of local
+// The block ELL, one workgroup per block (its halo in LDS), kEllLanes lanes a
+// row (a row's entries each take four dependent loads: 143,637 rows 62 us with
+// one lane, now 45): entry t of local
 // row p of block b at beoff[b] + t rows_b + p; the LDS slot of its column
 // (own row: its local row; another block's row: rows_b + its position in the
 // block's halo) and its value; the diagonal and the padding up to the block's
 // width point at the zero slot rows_b + halo_b with value 0.
+constexpr int kEllLanes = 16;
 __global__ void __launch_bounds__(kBlock) k_block_ell(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                       const double* __restrict__ val, const int32_t* __restrict__ perm,
                                                       const int32_t* __restrict__ iperm,
@@ -1477,14 +1480,14 @@ __global__ void __launch_bounds__(kBlock) k_block_ell(const int32_t* __restrict_
   for (int32_t k = threadIdx.x; k < nh; k += kBlock) hl[k] = hlist[h0 + k];
   __syncthreads();
   const int32_t pad = rows + nh, w = bw[b], e0 = beoff[b];
-  for (int32_t p = threadIdx.x; p < rows; p += kBlock) {
+  for (int32_t p = threadIdx.x / kEllLanes; p < rows; p += kBlock / kEllLanes) {
     const int32_t o = perm[brows[r0 + p]];
-    const int32_t len = rp[o + 1] - rp[o];
-    for (int32_t t = 0; t < w; ++t) {
+    const int32_t rb = rp[o], len = rp[o + 1] - rb;
+    for (int32_t t = threadIdx.x % kEllLanes; t < w; t += kEllLanes) {
       int32_t slot = pad;
       double v = 0.0;
       if (t < len) {
-        const int32_t e = rp[o] + t, oc = col[e];
+        const int32_t oc = col[rb + t];
         if (oc != o) {
           const int32_t j = iperm[oc];
           if (blk[j] == b) {
@@ -1497,7 +1500,7 @@ __global__ void __launch_bounds__(kBlock) k_block_ell(const int32_t* __restrict_
             }
             slot = rows + lo;
           }
-          v = val[e];
+          v = val[rb + t];
         }
       }
       elx[e0 + t * rows + p] = slot;
@@ -1553,14 +1556,11 @@ __global__ void k_block_values(const int32_t* rp, const int32_t* col, const doub
   const int32_t b = blockIdx.x;
   if (b >= nblk) return;
   const int32_t r0 = boff[b], rows = boff[b + 1] - r0, w = bw[b], e0 = beoff[b];
-  for (int32_t p = threadIdx.x; p < rows; p += blockDim.x) {
+  for (int32_t p = threadIdx.x / kEllLanes; p < rows; p += kBlock / kEllLanes) {
     const int32_t o = perm[brows[r0 + p]];
-    const int32_t len = rp[o + 1] - rp[o];
-    for (int32_t t = 0; t < w; ++t) {
-      double v = 0.0;
-      if (t < len && col[rp[o] + t] != o) v = val[rp[o] + t];
-      elv[e0 + t * rows + p] = v;
-    }
+    const int32_t rb = rp[o], len = rp[o + 1] - rb;
+    for (int32_t t = threadIdx.x % kEllLanes; t < w; t += kEllLanes)
+      elv[e0 + t * rows + p] = t < len && col[rb + t] != o ? val[rb + t] : 0.0;
   }
 }
 }  // namespace
