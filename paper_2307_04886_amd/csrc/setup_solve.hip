@@ -2071,7 +2071,7 @@ int32_t lanes_for(int32_t maxlen) {
 // nearly all, points in random order nearly none).  Sweeps do not depend on the
 // order within a colour.  1,000,000 points in random order, float: a colour 12.2 us,
 // now 7.0; A p in double 112 us, now 51.  (In grid order, 1,048,576 points: 5.2 us a
-// colour and 33 us, and nothing to gain.)
+// colour and 28 us, and nothing to gain.)
 int32_t* cluster_order(Handle& h, const Level& lv, const Level& nx) {
   hipStream_t s = h.stream;
   const int64_t n = lv.n, nc = nx.n;
