@@ -534,8 +534,9 @@ void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   }
   const Level& lv = h.L[l];
   const bool timed = !c.symmetric;            // the solve's cycle is the measured one
-  // on a coarse level the restriction into it already did the first colour
-  const int skip = l > 0 && folded_rows(h, l) > 0 ? 1 : 0;
+  // what sets x to zero already did the first colour: on a coarse level the
+  // restriction into it, on level 0 the start of a symmetric cycle
+  const int skip = (l > 0 || c.symmetric) && folded_rows(h, l) > 0 ? 1 : 0;
   const bool tail = (int)l >= h.tail_start;
   if (tail) {
     tail_sweeps(tail_pre_job(v, 1, h.opt.nu_pre, skip), tail_width(v.maxa), 1, s);
@@ -738,9 +739,7 @@ Cycle<V>& kry_ready(Handle& h) {
 // for the float cycle), the cycle starts from zero.
 template <class V>
 void kry_precondition(Handle& h, const Cycle<V>& c, hipStream_t s) {
-  const int64_t n = h.L[0].n;
-  if (std::is_same<V, float>::value) to_f32(h.kry.r, (float*)c.v[0].b, n, s);
-  fill_zero(c.v[0].x, n, s);
+  cycle_start(c.v[0], h.kry.r, folded_rows(h, 0), s);
   vcycle(h, c, 0, s);
 }
 
@@ -1086,8 +1085,7 @@ void precondition_noalloc(Handle& h, const double* r, double* z, int32_t precisi
   permute_in(l0.perm, r, sr, n, s);
   if (precision == GMG_PRECISION_F32) {
     const Cycle<float>& c = h.kry.c32;
-    to_f32(sr, (float*)c.v[0].b, n, s);
-    fill_zero(c.v[0].x, n, s);
+    cycle_start(c.v[0], sr, folded_rows(h, 0), s);
     vcycle(h, c, 0, s);
     permute_out(l0.perm, (const float*)c.v[0].x, z, n, s);
   } else {
@@ -1099,7 +1097,7 @@ void precondition_noalloc(Handle& h, const double* r, double* z, int32_t precisi
       h.noalloc_base = sr;
     }
     const Cycle<double>& c = h.noalloc64;
-    fill_zero(c.v[0].x, n, s);
+    cycle_start(c.v[0], sr, folded_rows(h, 0), s);
     vcycle(h, c, 0, s);
     permute_out(l0.perm, (const double*)c.v[0].x, z, n, s);
   }

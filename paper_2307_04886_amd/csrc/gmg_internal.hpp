@@ -622,6 +622,8 @@ void restrict_to(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s, 
 template <class V>
 void prolong_correct(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
 template <class V>
+void cycle_start(const LevelViewT<V>& v, const double* rhs, int32_t r0, hipStream_t s);
+template <class V>
 void fill_zero(V* p, int64_t n, hipStream_t s);
 void to_f32(const double* src, float* dst, int64_t n, hipStream_t s);
 void permute_in(const int32_t* perm, const double* src, double* dst, int64_t n, hipStream_t s);
