@@ -739,7 +739,7 @@ Cycle<V>& kry_ready(Handle& h) {
 // for the float cycle), the cycle starts from zero.
 template <class V>
 void kry_precondition(Handle& h, const Cycle<V>& c, hipStream_t s) {
-  cycle_start(c.v[0], h.kry.r, folded_rows(h, 0), s);
+  cycle_start(c.v[0], h.kry.r, folded_rows(h, 0), 1, s);
   vcycle(h, c, 0, s);
 }
 
@@ -900,11 +900,12 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   }
   const LevelViewT<V>& cv = c.v[l + 1];
   const Level& lv = h.L[l];
+  const int skip = l == 0 && folded_rows(h, l) > 0 ? 1 : 0;   // the first colour: done by the cycle's start
   const bool tail = (int)l >= h.tail_start;
   if (tail) {
-    tail_sweeps(tail_pre_job(v, kBatch, h.opt.nu_pre, 0), tail_width(v.maxa), kBatch, s);
+    tail_sweeps(tail_pre_job(v, kBatch, h.opt.nu_pre, skip), tail_width(v.maxa), kBatch, s);
   } else {
-    for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false);
+    for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false, k == 0 ? skip : 0);
     mresidual(v, s);
   }
   if (l + 2 == h.L.size() && cv.n <= kCoarseFusedBatch) {
@@ -923,9 +924,7 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
 
 template <class V>
 void bat_precondition(Handle& h, const Cycle<V>& c, hipStream_t s) {
-  const int64_t nk = h.L[0].n * kBatch;
-  if (std::is_same<V, float>::value) to_f32(h.bat.r, (float*)c.v[0].b, nk, s);
-  fill_zero(c.v[0].x, nk, s);
+  cycle_start(c.v[0], h.bat.r, folded_rows(h, 0), kBatch, s);
   mvcycle(h, c, 0, s);
 }
 
@@ -1085,7 +1084,7 @@ void precondition_noalloc(Handle& h, const double* r, double* z, int32_t precisi
   permute_in(l0.perm, r, sr, n, s);
   if (precision == GMG_PRECISION_F32) {
     const Cycle<float>& c = h.kry.c32;
-    cycle_start(c.v[0], sr, folded_rows(h, 0), s);
+    cycle_start(c.v[0], sr, folded_rows(h, 0), 1, s);
     vcycle(h, c, 0, s);
     permute_out(l0.perm, (const float*)c.v[0].x, z, n, s);
   } else {
@@ -1097,7 +1096,7 @@ void precondition_noalloc(Handle& h, const double* r, double* z, int32_t precisi
       h.noalloc_base = sr;
     }
     const Cycle<double>& c = h.noalloc64;
-    cycle_start(c.v[0], sr, folded_rows(h, 0), s);
+    cycle_start(c.v[0], sr, folded_rows(h, 0), 1, s);
     vcycle(h, c, 0, s);
     permute_out(l0.perm, (const double*)c.v[0].x, z, n, s);
   }
@@ -1748,7 +1747,7 @@ int gmg_solve_pcg(gmg_handle hh, const double* b_dev, double* x_dev, double tol,
       info->rel_residual = 0.0;
     }
     if (nb == 0.0) {
-      fill_zero(x_dev, n, s);
+      fill_f64(x_dev, 0.0, n, s);
       sync(s, "solve");
       if (info) info->converged = 1;
       h->stream = saved;

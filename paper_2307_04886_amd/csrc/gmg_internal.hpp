@@ -622,9 +622,7 @@ void restrict_to(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s, 
 template <class V>
 void prolong_correct(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t s);
 template <class V>
-void cycle_start(const LevelViewT<V>& v, const double* rhs, int32_t r0, hipStream_t s);
-template <class V>
-void fill_zero(V* p, int64_t n, hipStream_t s);
+void cycle_start(const LevelViewT<V>& v, const double* rhs, int32_t r0, int32_t vectors, hipStream_t s);
 void to_f32(const double* src, float* dst, int64_t n, hipStream_t s);
 void permute_in(const int32_t* perm, const double* src, double* dst, int64_t n, hipStream_t s);
 template <class V>
@@ -638,7 +636,7 @@ void pattern_outer(int64_t n, const int32_t* rp, const int32_t* col, const doubl
                    double scale, double* out, hipStream_t s);
 // batched right-hand sides (multi.hip): vectors [n][kBatch]
 template <class V>
-void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool descending);
+void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool descending, int skip = 0);
 template <class V>
 void mresidual(const LevelViewT<V>& v, hipStream_t s);
 template <class V>

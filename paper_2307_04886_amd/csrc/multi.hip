@@ -751,7 +751,7 @@ size_t mblock_lds(const BlockView<V>& B) {
 }
 
 template <class V>
-void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool descending) {
+void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool descending, int skip) {
   if (const size_t lds = mblock_lds(v.B)) {
     for (int k = 0; k < 4; ++k) {
       const int bc = descending ? 3 - k : k;
@@ -762,7 +762,7 @@ void mgs_sweep(const LevelViewT<V>& v, const Level& lv, hipStream_t s, bool desc
     return;
   }
   const int C = (int)lv.color_ptr.size() - 1;
-  for (int k = 0; k < C; ++k) {
+  for (int k = skip; k < C; ++k) {           // skip: first colours already done (ascending, not in block order)
     const int c = descending ? C - 1 - k : k;
     const int32_t r0 = lv.color_ptr[c], r1 = lv.color_ptr[c + 1];
     if (r1 <= r0) continue;
@@ -927,7 +927,7 @@ GMG_INSTANTIATE_GROUPED(float)
 #undef GMG_INSTANTIATE_GROUPED
 
 #define GMG_INSTANTIATE_MULTI(V)                                                                 \
-  template void mgs_sweep<V>(const LevelViewT<V>&, const Level&, hipStream_t, bool);            \
+  template void mgs_sweep<V>(const LevelViewT<V>&, const Level&, hipStream_t, bool, int);       \
   template void mresidual<V>(const LevelViewT<V>&, hipStream_t);                                \
   template void mrestrict<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);          \
   template void mprolong<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);           \

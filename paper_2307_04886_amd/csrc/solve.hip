@@ -318,12 +318,6 @@ __global__ void k_to_f32(const double* src, float* dst, int64_t n) {
   if (i < n) dst[i] = (float)src[i];
 }
 
-template <class V>
-__global__ void k_zero(V* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = V(0);
-}
-
 // The start of a symmetric cycle on level 0, from x = 0 with the right-hand side r
 // (float: rounded into b): the rows below r0, the first colour of the first sweep,
 // take their update at once, (b - 0) / A_rr, since every term of their sums is a
@@ -332,13 +326,15 @@ __global__ void k_zero(V* p, int64_t n) {
 // 1,000,000 in a cloud 3.4%).
 template <class V>
 __global__ void __launch_bounds__(kBlock) k_cycle_start(const double* __restrict__ r, const V* __restrict__ diag,
-                                                        V* __restrict__ b, V* __restrict__ x, int64_t n, int32_t r0) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+                                                        V* __restrict__ b, V* __restrict__ x, int64_t n, int32_t r0,
+                                                        int32_t vectors) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;   // row i of one of the interleaved vectors
+  if (t >= n * vectors) return;
+  const int32_t i = (int32_t)(vectors == 1 ? t : t / vectors);
   V v = V(0);
-  if (b || i < r0) v = (V)r[i];
-  if (b) b[i] = v;
-  x[i] = i < r0 ? v / diag[i] : V(0);
+  if (b || i < r0) v = (V)r[t];
+  if (b) b[t] = v;
+  x[t] = i < r0 ? v / diag[i] : V(0);
 }
 
 __global__ void k_check_finite(const double* v, int64_t n, int32_t* flag) {
@@ -475,14 +471,9 @@ void prolong_correct(const LevelViewT<V>& v, const LevelViewT<V>& c, hipStream_t
 // v.x and, in float, v.b for a cycle from zero with the right-hand side rhs (double:
 // v.b itself), the rows below r0 updated (k_cycle_start).
 template <class V>
-void cycle_start(const LevelViewT<V>& v, const double* rhs, int32_t r0, hipStream_t s) {
-  k_cycle_start<V><<<blocks_for(v.n), kBlock, 0, s>>>(rhs, v.diag, std::is_same<V, float>::value ? v.b : nullptr, v.x,
-                                                      v.n, r0);
-}
-
-template <class V>
-void fill_zero(V* p, int64_t n, hipStream_t s) {
-  k_zero<V><<<blocks_for(n), kBlock, 0, s>>>(p, n);
+void cycle_start(const LevelViewT<V>& v, const double* rhs, int32_t r0, int32_t vectors, hipStream_t s) {
+  k_cycle_start<V><<<blocks_for((int64_t)v.n * vectors), kBlock, 0, s>>>(
+      rhs, v.diag, std::is_same<V, float>::value ? v.b : nullptr, v.x, v.n, r0, vectors);
 }
 
 void to_f32(const double* src, float* dst, int64_t n, hipStream_t s) {
@@ -526,8 +517,7 @@ void check_finite(const double* v, int64_t n, int32_t* flag, hipStream_t s) {
   template void residual<V>(const LevelViewT<V>&, hipStream_t, bool);                                  \
   template void restrict_to<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t, int32_t);      \
   template void prolong_correct<V>(const LevelViewT<V>&, const LevelViewT<V>&, hipStream_t);           \
-  template void fill_zero<V>(V*, int64_t, hipStream_t);                                                \
-  template void cycle_start<V>(const LevelViewT<V>&, const double*, int32_t, hipStream_t);             \
+  template void cycle_start<V>(const LevelViewT<V>&, const double*, int32_t, int32_t, hipStream_t);    \
   template void permute_out<V>(const int32_t*, const V*, double*, int64_t, hipStream_t);
 GMG_INSTANTIATE(double)
 GMG_INSTANTIATE(float)
