@@ -539,7 +539,7 @@ void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const int skip = (l > 0 || c.symmetric) && folded_rows(h, l) > 0 ? 1 : 0;
   const bool tail = (int)l >= h.tail_start;
   if (tail) {
-    tail_sweeps(tail_pre_job(v, 1, h.opt.nu_pre, skip), tail_width(v.maxa), 1, s);
+    tail_sweeps(tail_pre_job(v, 1, h.opt.nu_pre, skip), tail_form(v.maxa), 1, s);
   } else {
     for (int k = 0; k < h.opt.nu_pre; ++k) gs_sweep(v, lv, s, l == 0, false, timed, k == 0 ? skip : 0);
     residual(v, s, l == 0);
@@ -547,7 +547,7 @@ void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   coarse_correction(h, c, l, s);
   const LevelViewT<V>& cv = c.v[l + 1];
   if (tail) {
-    tail_sweeps(tail_post_job(v, cv, 1, h.opt.nu_post, c.symmetric), tail_width(v.maxa), 1, s);
+    tail_sweeps(tail_post_job(v, cv, 1, h.opt.nu_post, c.symmetric), tail_form(v.maxa), 1, s);
   } else {
     prolong_correct(v, cv, s);
     for (int k = 0; k < h.opt.nu_post; ++k) gs_sweep(v, lv, s, l == 0, c.symmetric, timed);
@@ -903,7 +903,7 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const int skip = l == 0 && folded_rows(h, l) > 0 ? 1 : 0;   // the first colour: done by the cycle's start
   const bool tail = (int)l >= h.tail_start;
   if (tail) {
-    tail_sweeps(tail_pre_job(v, kBatch, h.opt.nu_pre, skip), tail_width(v.maxa), kBatch, s);
+    tail_sweeps(tail_pre_job(v, kBatch, h.opt.nu_pre, skip), tail_form(v.maxa), kBatch, s);
   } else {
     for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false, k == 0 ? skip : 0);
     mresidual(v, s);
@@ -915,7 +915,7 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
     mvcycle(h, c, l + 1, s);
   }
   if (tail) {
-    tail_sweeps(tail_post_job(v, cv, kBatch, h.opt.nu_post, c.symmetric), tail_width(v.maxa), kBatch, s);
+    tail_sweeps(tail_post_job(v, cv, kBatch, h.opt.nu_post, c.symmetric), tail_form(v.maxa), kBatch, s);
   } else {
     mprolong(v, cv, s);
     for (int k = 0; k < h.opt.nu_post; ++k) mgs_sweep(v, lv, s, c.symmetric);
@@ -1169,11 +1169,11 @@ struct GroupPlan {
   std::vector<RowStep<GResJob<V>>> residuals;
   std::vector<RowStep<GRestJob<V>>> restricts;
   std::vector<RowStep<GProlJob<V>>> prolongs;
-  // one-workgroup levels: the members' jobs of one row width
+  // one-workgroup levels: the members' jobs of one form
   struct TailStep {
     std::vector<TailJob<V>> jobs;
     std::vector<int32_t> members;
-    int32_t W = 0;
+    int32_t form = 0;
     int32_t nchunk = 0;
     size_t lds = 0;
     const TailJob<V>* djobs = nullptr;
@@ -1216,17 +1216,17 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
     P.order.push_back({GroupPlan<V>::RESTRICT, (int32_t)P.restricts.size()});
     P.restricts.push_back(std::move(rt));
   };
-  // the one-workgroup levels d above the coarsest, one step per row width
+  // the one-workgroup levels d above the coarsest, one step per form of the rows
   auto tail_step = [&](int d, bool is_post) {
-    for (int32_t W : {8, 16, kTailWMax}) {
+    for (int32_t form : {8, 16, kTailWMax, kTailLong}) {
       typename GroupPlan<V>::TailStep st;
-      st.W = W;
+      st.form = form;
       for (int m = 0; m < M; ++m) {
         const Handle& h = *H[m];
         const int l = (int)h.L.size() - 1 - d;
         if (l < ts[m]) continue;
         const LevelViewT<V>& v = C[m]->v[l];
-        if (tail_width(v.maxa) != W) continue;
+        if (tail_form(v.maxa) != form) continue;
         st.jobs.push_back(is_post ? tail_post_job(v, C[m]->v[l + 1], kBatch, h.opt.nu_post, true)
                                   : tail_pre_job(v, kBatch, h.opt.nu_pre, 0));
         st.members.push_back(m);
@@ -1371,7 +1371,7 @@ void group_iteration(const GroupPlan<V>& P, const int32_t* active, hipStream_t s
       }
       case GroupPlan<V>::TAIL: {
         const auto& t = P.tails[st.index];
-        gtail_sweeps(t.djobs, t.dmembers, (int32_t)t.jobs.size(), t.W, t.nchunk, t.lds, active, s);
+        gtail_sweeps(t.djobs, t.dmembers, (int32_t)t.jobs.size(), t.form, t.nchunk, t.lds, active, s);
         break;
       }
       case GroupPlan<V>::COARSE:

@@ -161,6 +161,7 @@ inline int blocks_for(int64_t n, int per_block = kBlock) {
 constexpr int64_t kTailRows = 4096;  // levels of at most this many rows are swept by one workgroup
 constexpr int kTailT = 512;          // its threads
 constexpr int kTailWMax = 32;        // entries of a row it holds at most
+constexpr int kTailLong = 64;        // the form of levels with longer rows (tail_form)
 constexpr int64_t kCoarseFused = 1024;   // coarsest rows up to which the restriction is fused with the solve
 // coarsest rows up to which that also holds for kBatch vectors of one hierarchy
 // (each workgroup restricts its vector; 226 rows: 10 us against 9 for the restriction
@@ -289,18 +290,25 @@ struct BlockView {
 };
 
 // A_l of a level swept by one workgroup (tail.hip): every colour's rows in
-// chunks of kWave, a row per lane, W = tail_width(longest row) entries.  Entry e
+// chunks of kWave, a row per lane, W = min(tail_form(longest row), kTailWMax) entries.  Entry e
 // of lane t's row in chunk q has its column, as a byte offset into a vector of
 // V, at ((q W/8 + e/8) kWave + t) 8 + e%8 and its value, in blocks of E = 16
 // bytes, at ((q W/E + e/E) kWave + t) E + e%E.  The diagonal and the padding
-// have column n (a zero behind the iterate).
+// have column n (a zero behind the iterate).  Entries past the first kTailWMax (form
+// kTailLong) lie in blocks of eight after one another, block g of a chunk's row t at
+// over[q] + g rows + t: its columns likewise, its values 16 bytes of the chunk's rows
+// next to one another.
 template <class V>
 struct TailRows {
   int32_t nchunk = 0;
-  const int4* chunk = nullptr;          // first row, rows, colour, entries of the longest row (a multiple of 8, at most W)
-  const int32_t* info = nullptr;        // [n] row length << 8 | entry of the diagonal (255: past the first W)
+  const int4* chunk = nullptr;          // first row, rows, colour, entries of the longest row (rounded up to a multiple of 8)
+  const int32_t* info = nullptr;        // [n] the diagonal's entry
   const uint16_t* col = nullptr;
   const V* val = nullptr;
+  const int32_t* over = nullptr;        // [nchunk + 1] a chunk's first block past the buffers (form kTailLong)
+  int32_t oblocks = 0;
+  const uint16_t* ocol = nullptr;
+  const V* oval = nullptr;
 };
 
 // What the V-cycle kernels need of one level (device pointers, new numbering),
@@ -343,7 +351,6 @@ struct TailJob {
   int32_t descending = 0;
   int32_t maxlen = 0;
   TailRows<V> A;
-  Sell<V> S;                            // A_l again: the entries of rows longer than the buffers
   const V* diag = nullptr;
   const V* b = nullptr;
   V* x = nullptr;
@@ -743,7 +750,9 @@ void gprolong(const GProlJob<V>* jobs, const GTile* tiles, int32_t ntiles, const
 template <class V>
 void gcoarse(const GCoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);
 // one-workgroup levels (tail.hip)
-int32_t tail_width(int32_t maxlen);                        // entries W held of rows of at most maxlen
+// How the rows of a level are held: 8, 16 or kTailWMax entries, or kTailLong where the
+// longest (maxlen) has more
+int32_t tail_form(int32_t maxlen);
 template <class V>
 size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc);
 // nu sweeps (the first `skip` colours of the first one done), then the residual
@@ -753,16 +762,17 @@ TailJob<V> tail_pre_job(const LevelViewT<V>& v, int32_t stride, int32_t nu, int3
 template <class V>
 TailJob<V> tail_post_job(const LevelViewT<V>& v, const LevelViewT<V>& c, int32_t stride, int32_t nu, bool descending);
 template <class V>
-void tail_sweeps(const TailJob<V>& J, int32_t W, int32_t vectors, hipStream_t s);
-// kBatch vectors of every listed member (jobs[i] is member members[i]'s; all of width W, at most nchunk chunks)
+void tail_sweeps(const TailJob<V>& J, int32_t form, int32_t vectors, hipStream_t s);
+// kBatch vectors of every listed member (jobs[i] is member members[i]'s; all of one form, at most nchunk chunks)
 template <class V>
-void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t W, int32_t nchunk, size_t lds,
+void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t form, int32_t nchunk, size_t lds,
                   const int32_t* active, hipStream_t s);
 int32_t coarse_rows(int64_t n);
 template <class V>
 void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s);
+void tail_over(const LevelView& v, int32_t nchunk, int32_t* blocks, hipStream_t s);   // blocks past the buffers of every chunk
 template <class V>
-void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s);
+void tail_fill(const LevelView& v, const TailRows<V>& R, hipStream_t s);
 // CG steps over the members' jobs (count of them); `tiles` cover each member's n * kBatch elements
 template <class V>
 void gkry_init(const GKryJob<V>* jobs, const GTile* tiles, int32_t ntiles, const int32_t* active, hipStream_t s);

@@ -2278,7 +2278,7 @@ template <class V>
 void tail_layout(Handle& h, const Level& lv, TailRows<V>& R) {
   const LevelView& v = lv.view;
   if (!R.col) {
-    const int32_t W = tail_width(v.maxa);
+    const int32_t W = std::min<int32_t>(tail_form(v.maxa), kTailWMax);
     R.nchunk = 0;
     for (size_t c = 0; c + 1 < lv.color_ptr.size(); ++c)
       R.nchunk += (lv.color_ptr[c + 1] - lv.color_ptr[c] + kWave - 1) / kWave;
@@ -2287,8 +2287,23 @@ void tail_layout(Handle& h, const Level& lv, TailRows<V>& R) {
     R.info = (int32_t*)dalloc(h, (size_t)lv.n * 4);
     R.col = (uint16_t*)dalloc(h, e * 2);
     R.val = (V*)dalloc(h, e * sizeof(V));
+    if (tail_form(v.maxa) == kTailLong) {
+      R.over = v.R.over;                       // the float copy: as the double one's
+      R.oblocks = v.R.oblocks;
+      if (!R.over) {
+        int32_t* blocks = (int32_t*)talloc(h.stream, (size_t)R.nchunk * 4);
+        int32_t* over = (int32_t*)dalloc(h, (size_t)(R.nchunk + 1) * 4);
+        tail_over(v, R.nchunk, blocks, h.stream);
+        scan_i32(blocks, over, R.nchunk, h.stream);
+        R.oblocks = (int32_t)read_i64(h, over + R.nchunk, 4);
+        R.over = over;
+        tfree(h.stream, blocks);
+      }
+      R.ocol = (uint16_t*)dalloc(h, (size_t)R.oblocks * 16);
+      R.oval = (V*)dalloc(h, (size_t)R.oblocks * 8 * sizeof(V));
+    }
   }
-  tail_fill<V>(v, R.nchunk, (int4*)R.chunk, (int32_t*)R.info, (uint16_t*)R.col, (V*)R.val, h.stream);
+  tail_fill<V>(v, R, h.stream);
 }
 template void tail_layout<double>(Handle&, const Level&, TailRows<double>&);
 template void tail_layout<float>(Handle&, const Level&, TailRows<float>&);

@@ -27,7 +27,10 @@ namespace {
 //    ones reload a buffer as soon as its rows are done, NB chunks of the
 //    wavefront (two to five phases each) ahead of their use;
 //  - a wavefront loads 16 bytes per lane and instruction, contiguous, and only
-//    as many entries as its chunk's longest row.
+//    as many entries as its chunk's longest row;
+//  - on levels with rows of more than 32 entries (hubs, dense graphs) a form of
+//    its own keeps one buffer and reads its rows' further entries in tiles of 16,
+//    two of them in flight from before the barrier that opens the phase.
 // Rows sum their terms in entry order; the diagonal entry points at a zero
 // kept behind x in the sweeps (its product is +0, which leaves the sum
 // unchanged: a sum that starts at +0 is never -0) and at the row itself in the
@@ -54,18 +57,22 @@ struct TailBuf {
   u32x4 c[W / 8];
   u32x4 v[W / E];
   V b, d;
-  int32_t info;                            // row length << 8 | entry of the diagonal
+  int32_t info;                            // the diagonal's entry
   int4 q;                                  // first row, rows, colour, entries of the longest row (all uniform)
-  __device__ __forceinline__ V value(int t) const {
-    const u32x4 a = v[t / E];
-    if constexpr (sizeof(V) == 8) {
-      return __builtin_bit_cast(V, (uint64_t)a[2 * (t % E) + 1] << 32 | a[2 * (t % E)]);
-    } else {
-      const uint32_t u = a[t % E];         // a value of its own: bit_cast of a vector's element takes the first
-      return __builtin_bit_cast(V, u);
-    }
-  }
 };
+
+// Value t of 16-byte blocks v.
+template <class V>
+__device__ __forceinline__ V tail_value(const u32x4* v, int t) {
+  constexpr int E = 16 / sizeof(V);
+  const u32x4 a = v[t / E];
+  if constexpr (sizeof(V) == 8) {
+    return __builtin_bit_cast(V, (uint64_t)a[2 * (t % E) + 1] << 32 | a[2 * (t % E)]);
+  } else {
+    const uint32_t u = a[t % E];           // a value of its own: bit_cast of a vector's element takes the first
+    return __builtin_bit_cast(V, u);
+  }
+}
 
 // Chunk `chunk`, whose entry of the chunk table is q.
 template <class V, int W>
@@ -98,18 +105,45 @@ __device__ __forceinline__ V lds_at(uint32_t o) {
   return *(const __attribute__((address_space(3))) V*)o;
 }
 
+// Two blocks of eight entries of the chunk's rows past their buffers.
+template <class V>
+struct TailTile {
+  static constexpr int E = 16 / sizeof(V);
+  u32x4 c[2], v[16 / E];
+};
+
+// Blocks g and g + 1 of the `blocks` past the buffers of the chunk in f, which begin
+// at block `over` of the level's: a row's 16 bytes next to the next row's.  Past the
+// last block the last again: the loads have no conditions, so that none waits for
+// another.
+template <class V, int W>
+__device__ __forceinline__ void tail_tile(const TailJob<V>& J, const TailBuf<V, W>& f, int32_t over, int32_t blocks,
+                                          int32_t g, TailTile<V>& t) {
+  constexpr int E = TailTile<V>::E, B = 8 / E;
+  const uint32_t lane = threadIdx.x & (kWave - 1), rows = (uint32_t)f.q.y, r = min(lane, rows - 1);
+  const Rsrc cr = make_rsrc(J.A.ocol, (int64_t)J.A.oblocks * 16);
+  const Rsrc vr = make_rsrc(J.A.oval, (int64_t)J.A.oblocks * (16 * B));
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t at = (uint32_t)over + (uint32_t)min(g + h, blocks - 1) * rows;
+    t.c[h] = bload16(cr, r * 16u, at * 16u);
+#pragma unroll
+    for (int u = 0; u < B; ++u) t.v[h * B + u] = bload16(vr, r * 16u, (at * B + u * rows) * 16u);
+  }
+}
+
 // sum of the row's terms in entry order; Res: the diagonal's included.  The
 // gathers of kTailGather entries are in flight together.
 constexpr int kTailGather = 16;
 template <bool Res, class V, int W>
-__device__ __forceinline__ V tail_sum(const TailJob<V>& J, const TailBuf<V, W>& f, int32_t row) {
+__device__ __forceinline__ V tail_sum(const TailBuf<V, W>& f, int32_t row) {
   constexpr int G = W < kTailGather ? W : kTailGather;
   // the width and the columns are kept as they are: without this the compiler
   // computes every resident row's conditions and addresses once, outside the
   // sweeps, and spills them
   int32_t w = uniform(f.q.w);
   asm volatile("" : "+s"(w));
-  const int32_t dp = f.info & 0xFF;
+  const int32_t dp = f.info;
   V s = V(0);
 #pragma unroll
   for (int g0 = 0; g0 < W; g0 += G) {
@@ -131,22 +165,50 @@ __device__ __forceinline__ V tail_sum(const TailJob<V>& J, const TailBuf<V, W>& 
       for (int h = 0; h < G; h += 8)
         if (g0 + h == 0 || g0 + h < w) {
 #pragma unroll
-          for (int u = 0; u < 8; ++u) s = s + f.value(g0 + h + u) * xv[h + u];
+          for (int u = 0; u < 8; ++u) s = s + tail_value<V>(f.v, g0 + h + u) * xv[h + u];
         }
     }
   }
-  if constexpr (W == kTailWMax) {
-    // rows longer than the buffers: their further entries from the SELL copy
-    if (J.maxlen > W) {
-      const int32_t len = f.info >> 8;
-      const int64_t base = J.S.ptr[row / kSlice] + (row & (kSlice - 1));
-      for (int32_t t = W; t < len; ++t) {
-        const int32_t j = J.S.col[base + (int64_t)t * kSlice];
-        const V v = J.S.val[base + (int64_t)t * kSlice];
-        if (Res || j != row) s = s + v * lds_at<V>((uint32_t)j * (uint32_t)sizeof(V));
+  return s;
+}
+
+// The sum s of a chunk's rows taken on over the entries past their buffers, from the
+// tiles a (blocks 0 and 1) and b (2 and 3), which it reads ahead of itself.  (Rows of
+// 64 entries, 37 colours of 600 points: 1.8 us a phase.  Read from the SELL copy, each
+// entry waiting for its column, these took 8.8, and four entries at a time in the
+// kernel before that 4.1; 400 points of 106 couplings: 2.3, 17 and 5.6.)
+template <bool Res, class V, int W>
+__device__ __forceinline__ V tail_rest(const TailJob<V>& J, const TailBuf<V, W>& f, int32_t row, int32_t over,
+                                       int32_t blocks, TailTile<V>& a, TailTile<V>& b, V s) {
+  const int32_t dp = f.info - W;
+  auto add = [&](const TailTile<V>& t, int32_t g) {
+    V xv[16];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (h == 0 || g + h < blocks) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          uint32_t o = (u & 1) ? t.c[h][u / 2] >> 16 : t.c[h][u / 2] & 0xFFFFu;
+          if constexpr (Res) o = 8 * (g + h) + u == dp ? (uint32_t)row * (uint32_t)sizeof(V) : o;
+          xv[8 * h + u] = lds_at<V>(o);
+        }
       }
-    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (h == 0 || g + h < blocks) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s = s + tail_value<V>(t.v, 8 * h + u) * xv[8 * h + u];
+      }
+  };
+  int32_t g = 0;
+  for (; g + 4 < blocks; g += 4) {
+    add(a, g);
+    tail_tile(J, f, over, blocks, g + 4, a);
+    add(b, g + 2);
+    tail_tile(J, f, over, blocks, g + 6, b);
   }
+  add(a, g);
+  if (g + 2 < blocks) add(b, g + 2);
   return s;
 }
 
@@ -161,7 +223,7 @@ __host__ __device__ constexpr int32_t tail_lds(int32_t n) {
 // when J.q_col is set, after them r = b - A x when J.r is set.  vec: the
 // vector's index in the interleaved arrays.  Phase p is colour p mod C of sweep
 // p / C; the residual follows the last phase.
-template <class V, int W, int NB, bool Stream>
+template <class V, int W, int NB, bool Stream, bool Long>
 __device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
   extern __shared__ double lds_raw[];
   V* xl = reinterpret_cast<V*>(lds_raw);                      // [n + 1]
@@ -232,32 +294,49 @@ __device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
     if (starts(i)) tail_load<V, W>(J, b, start_chunk(i), q0[i], buf[i]);
   // the chunk table in LDS: a later load must not wait for memory to learn its width
   int4* ct = reinterpret_cast<int4*>(reinterpret_cast<char*>(lds_raw) + tail_lds<V>(n));
+  int32_t* ot = reinterpret_cast<int32_t*>(ct + J.A.nchunk);  // Long: the chunks' first blocks past the buffers
   if constexpr (Stream)
     for (int32_t i = t; i < J.A.nchunk; i += kTailT) ct[i] = J.A.chunk[i];
+  if constexpr (Long)
+    for (int32_t i = t; i < J.A.nchunk; i += kTailT) ot[i] = J.A.over[i];
   __syncthreads();
   // phases done by the whole workgroup (one barrier ends each)
   int32_t phase = J.skip;
   auto reach = [&](int32_t p) {
     for (; phase < p; ++phase) __syncthreads();
   };
-  // the phase of the chunk in f in the sweep whose first phase is p0
-  auto phase_of = [&](const TailBuf<V, W>& f, int32_t p0) {
-    const int32_t c = uniform(f.q.z);
-    return p0 + (desc ? C - 1 - c : c);
-  };
-  auto sweep_chunk = [&](const TailBuf<V, W>& f, int32_t p) {
-    if (p < J.skip) return;
+  // the phase of colour c in the sweep whose first phase is p0; the colour of the wavefront's chunk k
+  auto phase_of = [&](int32_t c, int32_t p0) { return p0 + (desc ? C - 1 - c : c); };
+  auto colour_of = [&](int32_t k) { return uniform(ct[chunk_of(k)].z); };
+  // the chunk in f, the wavefront's k-th of the pass, in phase p: its rows swept, or
+  // (Res) their residuals
+  auto do_chunk = [&](auto res, const TailBuf<V, W>& f, int32_t k, int32_t p) {
+    constexpr bool Res = decltype(res)::value;
+    int32_t over = 0, blocks = 0;                             // past the buffers
+    TailTile<V> ta, tb;
+    if constexpr (Long) {
+      blocks = (f.q.w - W) / 8;
+      if (blocks > 0) {
+        over = uniform(ot[chunk_of(k)]);
+        tail_tile(J, f, over, blocks, 0, ta);
+        tail_tile(J, f, over, blocks, 2, tb);
+      }
+    }
     reach(p);
     if (lane < f.q.y) {
       const int32_t row = f.q.x + lane;
-      xl[row] = (f.b - tail_sum<false>(J, f, row)) / f.d;
+      V s = tail_sum<Res>(f, row);
+      if constexpr (Long)
+        if (blocks > 0) s = tail_rest<Res>(J, f, row, over, blocks, ta, tb, s);
+      if constexpr (Res) J.r[vec + (int64_t)row * K] = f.b - s;
+      else xl[row] = (f.b - s) / f.d;
     }
   };
-  auto residual_chunk = [&](const TailBuf<V, W>& f) {
-    if (lane < f.q.y) {
-      const int32_t row = f.q.x + lane;
-      J.r[vec + (int64_t)row * K] = f.b - tail_sum<true>(J, f, row);
-    }
+  auto sweep_chunk = [&](const TailBuf<V, W>& f, int32_t k, int32_t p) {
+    if (p >= J.skip) do_chunk(std::integral_constant<bool, false>{}, f, k, p);
+  };
+  auto residual_chunk = [&](const TailBuf<V, W>& f, int32_t k, int32_t p) {
+    do_chunk(std::integral_constant<bool, true>{}, f, k, p);
   };
   const int32_t end = J.nsweeps * C;
   if constexpr (Stream) {
@@ -268,14 +347,13 @@ __device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
       for (int i = 0; i < NB; ++i) {
         if (left > 0) {
           if (p0 < end) {
-            const int32_t p = phase_of(buf[i], p0);
-            sweep_chunk(buf[i], p);
+            const int32_t p = phase_of(uniform(buf[i].q.z), p0);
+            sweep_chunk(buf[i], k, p);
             // end the phase before the reload when the wavefront's next chunk
             // is in a later one: the others need not wait for its loads to issue
-            if (p >= J.skip && (left == 1 || k + 1 == mine || phase_of(buf[(i + 1) % NB], p0) > p)) reach(p + 1);
+            if (p >= J.skip && (left == 1 || k + 1 == mine || phase_of(NB > 1 ? uniform(buf[(i + 1) % NB].q.z) : colour_of(k + 1), p0) > p)) reach(p + 1);
           } else {
-            reach(end);
-            residual_chunk(buf[i]);
+            residual_chunk(buf[i], k, end);
           }
           if (left > NB) tail_load<V, W>(J, b, chunk_of(ahead), ct[chunk_of(ahead)], buf[i]);
           ahead = ahead + 1 == mine ? 0 : ahead + 1;
@@ -292,32 +370,32 @@ __device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
     for (int32_t p0 = 0; p0 < end; p0 += C) {
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        if (i < mine) sweep_chunk(buf[i], phase_of(buf[i], p0));
+        if (i < mine) sweep_chunk(buf[i], i, phase_of(uniform(buf[i].q.z), p0));
     }
     reach(end);
     if (J.r) {
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        if (i < mine) residual_chunk(buf[i]);
+        if (i < mine) residual_chunk(buf[i], i, end);
     }
   }
   for (int32_t i = t; i < n; i += kTailT) x[(int64_t)i * K] = xl[i];
 }
 
-template <class V, int W, int NB, bool Stream>
+template <class V, int W, int NB, bool Stream, bool Long>
 __global__ void __launch_bounds__(kTailT) k_tail(TailJob<V> J) {
-  tail_run<V, W, NB, Stream>(J, (int32_t)blockIdx.x);
+  tail_run<V, W, NB, Stream, Long>(J, (int32_t)blockIdx.x);
 }
 
 // Grouped: job blockIdx.x / kBatch of the list, vector blockIdx.x % kBatch.
-template <class V, int W, int NB, bool Stream>
+template <class V, int W, int NB, bool Stream, bool Long>
 __global__ void __launch_bounds__(kTailT) k_gtail(const TailJob<V>* __restrict__ jobs,
                                                   const int32_t* __restrict__ members,
                                                   const int32_t* __restrict__ active) {
   const int32_t i = uniform((int32_t)blockIdx.x / kBatch);
   if (!active[members[i]]) return;
   const TailJob<V> J = jobs[i];
-  tail_run<V, W, NB, Stream>(J, (int32_t)blockIdx.x % kBatch);
+  tail_run<V, W, NB, Stream, Long>(J, (int32_t)blockIdx.x % kBatch);
 }
 
 // b_c = P^T r (or b_c given, when the job has no P^T) and x_c = A_c^-1 b_c in
@@ -425,17 +503,9 @@ __global__ void GMG_COARSE_BOUNDS k_coarse(CoarseJob<V> J) {
   coarse_run<V, R>(J, (int32_t)blockIdx.x, (int32_t)blockIdx.y);
 }
 
-// A_l (SELL, double) into the chunks' layout with values in V, a wavefront per
-// chunk: its place in the colours, then a row per lane, padding with the zero
-// behind the iterate and value 0.
-template <class V, int W>
-__global__ void __launch_bounds__(kBlock) k_tail_fill(SellView A, const int32_t* __restrict__ cptr, int32_t C, int32_t n,
-                                                      int32_t nchunk, int4* __restrict__ chunk,
-                                                      int32_t* __restrict__ info, u32x4* __restrict__ col,
-                                                      V* __restrict__ val) {
-  constexpr int E = TailBuf<V, W>::E;
-  const int32_t q = uniform((int32_t)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
-  if (q >= nchunk) return;
+// Chunk q of a level whose colours begin at cptr[0 .. C]: its first row, rows, colour
+// and the entries of its longest row, rounded up to a multiple of 8.
+__device__ __forceinline__ int4 tail_chunk(const SellView& A, const int32_t* __restrict__ cptr, int32_t C, int32_t q) {
   const int lane = threadIdx.x & (kWave - 1);
   int32_t c = 0, before = 0, lo = 0, hi = 0;       // the colour that holds chunk q
   for (; c < C; ++c) {
@@ -445,17 +515,48 @@ __global__ void __launch_bounds__(kBlock) k_tail_fill(SellView A, const int32_t*
     if (q < before + m) break;
     before += m;
   }
-  const int32_t r0 = lo + (q - before) * kWave, rows = min(hi - r0, kWave), r = r0 + lane;
+  const int32_t r0 = lo + (q - before) * kWave, rows = min(hi - r0, kWave);
+  int32_t w = lane < rows ? A.len[r0 + lane] : 0;
+  for (int o = kWave / 2; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o, kWave));
+  return int4{r0, rows, c, (w + 7) & ~7};
+}
+
+__device__ __forceinline__ int32_t tail_chunk_index() {
+  return uniform((int32_t)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+}
+
+// The blocks of eight entries that every chunk's rows have past the first kTailWMax.
+__global__ void __launch_bounds__(kBlock) k_tail_over(SellView A, const int32_t* __restrict__ cptr, int32_t C,
+                                                      int32_t nchunk, int32_t* __restrict__ blocks) {
+  const int32_t q = tail_chunk_index();
+  if (q >= nchunk) return;
+  const int4 k = tail_chunk(A, cptr, C, q);
+  if ((threadIdx.x & (kWave - 1)) == 0) blocks[q] = max(0, (k.w - kTailWMax) / 8) * k.y;
+}
+
+// A_l (SELL, double) into the chunks' layout with values in V, a wavefront per
+// chunk: its place in the colours, then a row per lane, padding with the zero
+// behind the iterate and value 0.  The blocks past the buffers go round the grid's
+// second dimension.
+template <class V, int W>
+__global__ void __launch_bounds__(kBlock) k_tail_fill(SellView A, const int32_t* __restrict__ cptr, int32_t C, int32_t n,
+                                                      int32_t nchunk, int4* __restrict__ chunk,
+                                                      int32_t* __restrict__ info, u32x4* __restrict__ col,
+                                                      V* __restrict__ val, const int32_t* __restrict__ over,
+                                                      u32x4* __restrict__ ocol, V* __restrict__ oval) {
+  constexpr int E = 16 / sizeof(V);
+  const int32_t q = tail_chunk_index();
+  if (q >= nchunk) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int4 k = tail_chunk(A, cptr, C, q);
+  const int32_t rows = k.y, r = k.x + lane;
   const bool on = lane < rows;
   const int32_t len = on ? A.len[r] : 0;
-  int32_t w = len;
-  for (int o = kWave / 2; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o, kWave));
-  w = min((w + 7) & ~7, W);
-  if (lane == 0) chunk[q] = int4{r0, rows, c, w};
+  if (lane == 0 && blockIdx.y == 0) chunk[q] = k;
   const int64_t base = on ? A.ptr[r / kSlice] + (r & (kSlice - 1)) : 0;
-  int32_t dp = 0xFF;
-#pragma unroll
-  for (int e0 = 0; e0 < W; e0 += 8) {
+  int32_t dp = -1;
+  // entries e0 .. e0 + 7 of the row: a block of columns, 8 / E of values (v_at: the place of the h-th)
+  auto block = [&](int32_t e0, u32x4& cols, auto v_at) {
     uint32_t o[8];
     V v[8];
 #pragma unroll
@@ -469,16 +570,28 @@ __global__ void __launch_bounds__(kBlock) k_tail_fill(SellView A, const int32_t*
       }
       o[u] = (uint32_t)j * (uint32_t)sizeof(V);
     }
-    u32x4 cw;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) cw[u] = o[2 * u] | o[2 * u + 1] << 16;
-    col[((int64_t)q * (W / 8) + e0 / 8) * kWave + lane] = cw;
+    for (int u = 0; u < 4; ++u) cols[u] = o[2 * u] | o[2 * u + 1] << 16;
 #pragma unroll
     for (int h = 0; h < 8 / E; ++h)
 #pragma unroll
-      for (int u = 0; u < E; ++u) val[(((int64_t)q * (W / E) + e0 / E + h) * kWave + lane) * E + u] = v[h * E + u];
+      for (int u = 0; u < E; ++u) v_at(h)[u] = v[h * E + u];
+  };
+#pragma unroll
+  for (int e0 = 0; e0 < W; e0 += 8) {
+    if (blockIdx.y > 0) break;
+    u32x4 cw;
+    block(e0, cw, [&](int h) { return val + (((int64_t)q * (W / E) + e0 / E + h) * kWave + lane) * E; });
+    col[((int64_t)q * (W / 8) + e0 / 8) * kWave + lane] = cw;
   }
-  if (on) info[r] = len << 8 | dp;
+  if (over && on)
+    for (int32_t g = (int32_t)blockIdx.y; W + 8 * g < k.w; g += (int32_t)gridDim.y) {
+      const int64_t at = (int64_t)over[q] + (int64_t)g * rows;
+      u32x4 cw;
+      block(W + 8 * g, cw, [&](int h) { return oval + (at * (8 / E) + (int64_t)h * rows + lane) * E; });
+      ocol[at + lane] = cw;
+    }
+  if (on && dp >= 0) info[r] = dp;
 }
 
 // Row buffers of a wavefront: what a thread's 256 registers take beside the
@@ -490,35 +603,36 @@ constexpr int tail_buffers() {
   return W == 8 ? (Stream ? 4 : 8) : W == 16 ? (Stream ? 4 : 6) : (Stream ? 2 : 3);
 }
 
-// Calls f(W, NB, Stream) as integral constants for levels of nchunk chunks (the
-// most of a group) and row width W.
+// Calls f(W, NB, Stream, Long) as integral constants for levels of nchunk chunks
+// (the most of a group) and the form of tail_form.
 template <class V, class F>
-void with_tail(int32_t W, int32_t nchunk, F&& f) {
+void with_tail(int32_t form, int32_t nchunk, F&& f) {
+  const std::integral_constant<bool, true> yes;
+  const std::integral_constant<bool, false> no;
   auto go = [&](auto WC) {
     constexpr int w = decltype(WC)::value;
     const std::integral_constant<int, tail_buffers<V, w, false>()> resident;
-    {
-      if (nchunk > resident.value * (kTailT / kWave)) {
-        f(WC, std::integral_constant<int, tail_buffers<V, w, true>()>{}, std::integral_constant<bool, true>{});
-        return;
-      }
-    }
-    f(WC, resident, std::integral_constant<bool, false>{});
+    if (nchunk > resident.value * (kTailT / kWave))
+      f(WC, std::integral_constant<int, tail_buffers<V, w, true>()>{}, yes, no);
+    else
+      f(WC, resident, no, no);
   };
-  switch (W) {
+  switch (form) {
     case 8: go(std::integral_constant<int, 8>{}); break;
     case 16: go(std::integral_constant<int, 16>{}); break;
-    default: go(std::integral_constant<int, 32>{}); break;
+    case kTailWMax: go(std::integral_constant<int, kTailWMax>{}); break;
+    default:                               // one buffer beside the two tiles (two do not fit 256 registers in double)
+      f(std::integral_constant<int, kTailWMax>{}, std::integral_constant<int, 1>{}, yes, yes);
   }
 }
 
 }  // namespace
 
-int32_t tail_width(int32_t maxlen) { return maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : kTailWMax; }
+int32_t tail_form(int32_t maxlen) { return maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= kTailWMax ? kTailWMax : kTailLong; }
 
 template <class V>
 size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc) {
-  return (size_t)tail_lds<V>(n) + std::max((size_t)A.nchunk * sizeof(int4), (size_t)nc * sizeof(V));
+  return (size_t)tail_lds<V>(n) + std::max((size_t)A.nchunk * (sizeof(int4) + (A.over ? 4 : 0)), (size_t)nc * sizeof(V));
 }
 
 template <class V>
@@ -529,7 +643,6 @@ TailJob<V> tail_job(const LevelViewT<V>& v, int32_t stride) {
   J.stride = stride;
   J.maxlen = v.maxa;
   J.A = v.R;
-  J.S = v.A;
   J.diag = v.diag;
   J.b = v.b;
   J.x = v.x;
@@ -560,21 +673,22 @@ TailJob<V> tail_post_job(const LevelViewT<V>& v, const LevelViewT<V>& c, int32_t
 }
 
 template <class V>
-void tail_sweeps(const TailJob<V>& J, int32_t W, int32_t vectors, hipStream_t s) {
-  if (!J.A.col || W != tail_width(J.maxlen) || J.n > kTailRows)
+void tail_sweeps(const TailJob<V>& J, int32_t form, int32_t vectors, hipStream_t s) {
+  if (!J.A.col || form != tail_form(J.maxlen) || J.n > kTailRows)
     throw Error{GMG_DEVICE_ERROR, "tail level without its row layout"};
-  with_tail<V>(W, J.A.nchunk, [&](auto WC, auto BC, auto SC) {
-    k_tail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value>
+  with_tail<V>(form, J.A.nchunk, [&](auto WC, auto BC, auto SC, auto LC) {
+    k_tail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value, decltype(LC)::value>
         <<<vectors, kTailT, tail_lds_bytes(J.A, J.n, J.nc), s>>>(J);
   });
 }
 
 template <class V>
-void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t W, int32_t nchunk, size_t lds,
+void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count, int32_t form, int32_t nchunk, size_t lds,
                   const int32_t* active, hipStream_t s) {
   if (count <= 0) return;
-  with_tail<V>(W, nchunk, [&](auto WC, auto BC, auto SC) {
-    k_gtail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value><<<count * kBatch, kTailT, lds, s>>>(jobs, members, active);
+  with_tail<V>(form, nchunk, [&](auto WC, auto BC, auto SC, auto LC) {
+    k_gtail<V, decltype(WC)::value, decltype(BC)::value, decltype(SC)::value, decltype(LC)::value>
+        <<<count * kBatch, kTailT, lds, s>>>(jobs, members, active);
   });
 }
 
@@ -605,16 +719,21 @@ void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
   });
 }
 
+void tail_over(const LevelView& v, int32_t nchunk, int32_t* blocks, hipStream_t s) {
+  k_tail_over<<<blocks_for(nchunk, kBlock / kWave), kBlock, 0, s>>>(v.A, v.cptr, v.ncolors, nchunk, blocks);
+}
+
 template <class V>
-void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, uint16_t* col, V* val, hipStream_t s) {
+void tail_fill(const LevelView& v, const TailRows<V>& R, hipStream_t s) {
   auto go = [&](auto WC) {
-    k_tail_fill<V, decltype(WC)::value><<<blocks_for(nchunk, kBlock / kWave), kBlock, 0, s>>>(
-        v.A, v.cptr, v.ncolors, v.n, nchunk, chunk, info, reinterpret_cast<u32x4*>(col), val);
+    k_tail_fill<V, decltype(WC)::value><<<dim3(blocks_for(R.nchunk, kBlock / kWave), R.over ? 16 : 1), kBlock, 0, s>>>(
+        v.A, v.cptr, v.ncolors, v.n, R.nchunk, (int4*)R.chunk, (int32_t*)R.info, (u32x4*)R.col, (V*)R.val, R.over,
+        (u32x4*)R.ocol, (V*)R.oval);
   };
-  switch (tail_width(v.maxa)) {
+  switch (tail_form(v.maxa)) {
     case 8: go(std::integral_constant<int, 8>{}); break;
     case 16: go(std::integral_constant<int, 16>{}); break;
-    default: go(std::integral_constant<int, 32>{}); break;
+    default: go(std::integral_constant<int, kTailWMax>{}); break;
   }
 }
 
@@ -626,7 +745,7 @@ void tail_fill(const LevelView& v, int32_t nchunk, int4* chunk, int32_t* info, u
   template void gtail_sweeps<V>(const TailJob<V>*, const int32_t*, int32_t, int32_t, int32_t, size_t, const int32_t*,   \
                                 hipStream_t);                                                                  \
   template void coarse_fused<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                     \
-  template void tail_fill<V>(const LevelView&, int32_t, int4*, int32_t*, uint16_t*, V*, hipStream_t);
+  template void tail_fill<V>(const LevelView&, const TailRows<V>&, hipStream_t);
 GMG_INSTANTIATE_TAIL(double)
 GMG_INSTANTIATE_TAIL(float)
 #undef GMG_INSTANTIATE_TAIL
