@@ -413,6 +413,29 @@ constexpr int kCoarseChunk = 16;           // entries of a row of P^T whose load
 #define GMG_COARSE_BOUNDS __launch_bounds__(kTailT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 __host__ __device__ constexpr int32_t coarse_up(int32_t n) { return (n + kCoarseAhead - 1) / kCoarseAhead * kCoarseAhead; }
 
+// acc and the `up` (a multiple of kCoarseAhead) products p, R apart, one after another.
+template <int R>
+__device__ __forceinline__ double coarse_add(double acc, const double* p, int32_t up) {
+  const double* p0 = p;
+  double q[2][kCoarseAhead];
+#pragma unroll
+  for (int u = 0; u < kCoarseAhead; ++u) q[0][u] = p[u * R];
+  for (int32_t k = 0; k < up; k += 2 * kCoarseAhead) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      // the block after this one (past the end: the first again, not added)
+      p = k + (h + 1) * kCoarseAhead < up ? p + kCoarseAhead * R : p0;
+#pragma unroll
+      for (int u = 0; u < kCoarseAhead; ++u) q[1 - h][u] = p[u * R];
+      if (h == 0 || k + kCoarseAhead < up) {
+#pragma unroll
+        for (int u = 0; u < kCoarseAhead; ++u) acc = acc + q[h][u];
+      }
+    }
+  }
+  return acc;
+}
+
 template <class V, int R>
 __device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group, int32_t vec) {
   extern __shared__ double lds_raw[];
@@ -476,24 +499,7 @@ __device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group,
   if (total + t < up * R) m[total + t] = 0.0;
   __syncthreads();
   if (t < R && i0 + t < n) {
-    double acc = 0.0;
-    const double* p = m + t;
-    double q[2][kCoarseAhead];
-#pragma unroll
-    for (int u = 0; u < kCoarseAhead; ++u) q[0][u] = p[u * R];
-    for (int32_t k = 0; k < up; k += 2 * kCoarseAhead) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        // the block after this one (past the end: the first again, not added)
-        p = k + (h + 1) * kCoarseAhead < up ? p + kCoarseAhead * R : m + t;
-#pragma unroll
-        for (int u = 0; u < kCoarseAhead; ++u) q[1 - h][u] = p[u * R];
-        if (h == 0 || k + kCoarseAhead < up) {
-#pragma unroll
-          for (int u = 0; u < kCoarseAhead; ++u) acc = acc + q[h][u];
-        }
-      }
-    }
+    const double acc = coarse_add<R>(0.0, m + t, up);
     J.x[vec + (int64_t)(i0 + t) * K] = (V)acc;
   }
 }
@@ -532,6 +538,49 @@ __global__ void __launch_bounds__(kBlock) k_tail_over(SellView A, const int32_t*
   if (q >= nchunk) return;
   const int4 k = tail_chunk(A, cptr, C, q);
   if ((threadIdx.x & (kWave - 1)) == 0) blocks[q] = max(0, (k.w - kTailWMax) / 8) * k.y;
+}
+
+// The same solve (b given) for coarsest levels of more than kCoarseFused rows, of which
+// a workgroup of coarse_run could take four at most with all their columns: kWideRows
+// rows of a vector a workgroup, the columns in tiles of kWideCols, the next tile's loads
+// in flight while one lane a row adds the products of one.  A direct solve of 1,100 rows
+// takes 51 us in all, 2,000 61 and 4,032 84 (four or two rows a workgroup, a part of a
+// cache line each: 59, 87 and 385; one lane a row from memory, 84, 125 and 212).
+constexpr int kWideRows = 16, kWideCols = kCoarseM * kTailT / kWideRows;
+template <class V>
+__global__ void GMG_COARSE_BOUNDS k_coarse_wide(CoarseJob<V> J) {
+  extern __shared__ double lds_raw[];
+  constexpr int R = kWideRows;
+  double* bc = lds_raw;                    // [kWideCols]
+  double* m = lds_raw + kWideCols;         // [kWideCols][R]
+  const int32_t n = J.n, K = J.stride, t = threadIdx.x, i0 = (int32_t)blockIdx.x * R, vec = (int32_t)blockIdx.y;
+  const int64_t ld = inv_ld(n);
+  double a[kCoarseM];
+  V bv;
+  auto load = [&](int32_t c0) {
+#pragma unroll
+    for (int u = 0; u < kCoarseM; ++u) {
+      const int32_t e = u * kTailT + t;
+      a[u] = J.M[(int64_t)min(c0 + e / R, n - 1) * ld + min(i0 + (e & (R - 1)), n - 1)];
+    }
+    bv = J.b[vec + (int64_t)min(c0 + t, n - 1) * K];
+  };
+  static_assert(kWideCols == kTailT, "a right-hand side per thread");
+  load(0);
+  double acc = 0.0;
+  for (int32_t c0 = 0; c0 < n; c0 += kWideCols) {
+    bc[t] = (double)bv;
+    __syncthreads();                       // and the last tile's products are added
+#pragma unroll
+    for (int u = 0; u < kCoarseM; ++u) {
+      const int32_t e = u * kTailT + t;
+      m[e] = c0 + e / R < n ? a[u] * bc[e / R] : 0.0;
+    }
+    __syncthreads();
+    load(min(c0 + kWideCols, n - 1));
+    if (t < R) acc = coarse_add<R>(acc, m + t, coarse_up(min(kWideCols, n - c0)));
+  }
+  if (t < R && i0 + t < n) J.x[vec + (int64_t)(i0 + t) * K] = (V)acc;
 }
 
 // A_l (SELL, double) into the chunks' layout with values in V, a wavefront per
@@ -692,10 +741,10 @@ void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count,
   });
 }
 
-// Rows a workgroup of the coarsest solve takes: kCoarseM elements of the inverse
-// a thread, at most 64 KiB in LDS.  More rows per workgroup mean fewer copies of
-// the restriction, fewer mean more load paths.
-int32_t coarse_rows(int64_t n) { return n <= 512 ? 16 : n <= 1024 ? 8 : n <= 2048 ? 4 : 2; }
+// Rows a workgroup of the coarsest solve of up to kCoarseFused takes: kCoarseM elements
+// of the inverse a thread, at most 64 KiB in LDS.  More rows per workgroup mean fewer
+// copies of the restriction, fewer mean more load paths.
+int32_t coarse_rows(int64_t n) { return n <= 512 ? 16 : 8; }
 template <class V>
 size_t coarse_lds(const CoarseJob<V>& J) {
   return (size_t)coarse_up(J.n) * 8 * (1 + J.rows) + (J.staged ? (size_t)J.nf * sizeof(V) : 0);
@@ -706,14 +755,18 @@ template <class F>
 void with_rows(int32_t R, F&& f) {
   switch (R) {
     case 16: f(std::integral_constant<int, 16>{}); break;
-    case 8: f(std::integral_constant<int, 8>{}); break;
-    case 4: f(std::integral_constant<int, 4>{}); break;
-    default: f(std::integral_constant<int, 2>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
   }
 }
 
 template <class V>
 void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
+  if (J.n > kCoarseFused) {
+    if (J.T.ptr) throw Error{GMG_DEVICE_ERROR, "coarsest level too large to restrict in its solve"};
+    k_coarse_wide<V><<<dim3((J.n + kWideRows - 1) / kWideRows, vectors), kTailT,
+                       (size_t)kWideCols * (1 + kWideRows) * 8, s>>>(J);
+    return;
+  }
   with_rows(J.rows, [&](auto RC) {
     k_coarse<V, decltype(RC)::value><<<dim3((J.n + J.rows - 1) / J.rows, vectors), kTailT, coarse_lds(J), s>>>(J);
   });
