@@ -326,6 +326,13 @@ int gmg_level_sizes(gmg_handle h, int32_t level, int64_t* sizes_host);
  */
 int gmg_level_tuning(gmg_handle h, int32_t level, int32_t* out_host);
 
+/*
+ * The forms of the cycles that level l's sizes choose, written to out_host[0..1]:
+ *  0 and 1 one if the batched cycle in float (0) and in double (1) restricts from
+ *    this level in the coarsest level's solve.
+ */
+int gmg_level_routes(gmg_handle h, int32_t level, int32_t* out_host);
+
 /* Export codes of gmg_export_level (element type and count for level l). */
 enum gmg_export_what {
   GMG_EXPORT_POSITIONS = 0,    /* double[n*3] points of the level */

@@ -29,7 +29,7 @@ EXPORTS = {
 # Symbols the library exports (checked on load).
 SYMBOLS = ["gmg_default_options", "gmg_build_hierarchy", "gmg_solve", "gmg_solve_pcg", "gmg_precondition",
            "gmg_update_matrix", "gmg_pattern_outer", "gmg_solve_pcg_batched", "gmg_solve_pcg_grouped", "gmg_precondition_batched", "gmg_precondition_noalloc", "gmg_free", "gmg_status_string", "gmg_last_error",
-           "gmg_num_levels", "gmg_level_sizes", "gmg_level_tuning", "gmg_export_level", "gmg_timer_start", "gmg_timer_stop"]
+           "gmg_num_levels", "gmg_level_sizes", "gmg_level_tuning", "gmg_level_routes", "gmg_export_level", "gmg_timer_start", "gmg_timer_stop"]
 
 # gmg_precision
 PRECISION = {"f64": 0, "f32": 1}
@@ -95,6 +95,7 @@ def library():
     L.gmg_level_sizes.argtypes = [P, I32, P]
     L.gmg_export_level.argtypes = [P, I32, I32, P, I64]
     L.gmg_level_tuning.argtypes = [P, I32, P]
+    L.gmg_level_routes.argtypes = [P, I32, P]
     L.gmg_timer_start.argtypes = [I32, I32]
     L.gmg_timer_stop.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(I64),
                                  ctypes.POINTER(ctypes.c_double)]
@@ -193,6 +194,14 @@ class Hierarchy:
             raise _err(st)
         return dict(lanes_A=int(t[0]), lanes_PT=int(t[1]), chunk=int(t[2]), block_sweep=int(t[3]),
                     uniform_width=int(t[4]))
+
+    def routes(self, level):
+        """gmg_level_routes: the forms of the cycles that the level's sizes choose."""
+        t = np.zeros(2, dtype=np.int32)
+        st = library().gmg_level_routes(self._h, level, t.ctypes.data_as(ctypes.c_void_p))
+        if st:
+            raise _err(st)
+        return dict(coarse_fused_f32=bool(t[0]), coarse_fused_f64=bool(t[1]))
 
     def export(self, level, what):
         code, dt = EXPORTS[what]

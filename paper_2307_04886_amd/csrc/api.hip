@@ -500,10 +500,8 @@ int32_t folded_rows(const Handle& h, size_t l) {
   return lv.color_ptr[1];
 }
 
-// The coarsest solve of a cycle, x_c = A_c^-1 b_c; with fine given (and the
-// coarsest level small enough) b_c = P^T r is formed by the same kernel.
-inline bool coarse_fuses(const Handle& h) { return h.L.back().n <= kCoarseFused; }
-
+// The coarsest solve of a cycle, x_c = A_c^-1 b_c; with fine given b_c = P^T r is
+// formed by the same kernel.
 template <class V>
 CoarseJob<V> coarse_job(const Handle& h, const LevelViewT<V>* fine, const LevelViewT<V>& c, int32_t stride) {
   CoarseJob<V> J;
@@ -515,21 +513,22 @@ CoarseJob<V> coarse_job(const Handle& h, const LevelViewT<V>* fine, const LevelV
     J.T = fine->T;
     J.r = fine->r;
     J.nf = fine->n;
-    J.staged = (int64_t)fine->n * (int64_t)sizeof(V) <= kCoarseStaged ? 1 : 0;
   }
   J.b = c.b;
   J.x = c.x;
   return J;
 }
 
-template <class V>
-void coarse_correction(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s);
+// Whether the batched cycle restricts into the coarsest level in its solve (kCoarseFused).
+inline bool coarse_fuses(int64_t fine_rows, int64_t coarse_rows, int64_t value_bytes) {
+  return coarse_rows <= kCoarseFused && fine_rows * value_bytes <= kCoarseStaged;
+}
 
 template <class V>
 void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   const LevelViewT<V>& v = c.v[l];
   if (l + 1 == h.L.size()) {
-    coarse_fused(coarse_job<V>(h, nullptr, v, 1), 1, s);
+    coarse_solve(coarse_job<V>(h, nullptr, v, 1), 1, s);
     return;
   }
   const Level& lv = h.L[l];
@@ -544,8 +543,9 @@ void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
     for (int k = 0; k < h.opt.nu_pre; ++k) gs_sweep(v, lv, s, l == 0, false, timed, k == 0 ? skip : 0);
     residual(v, s, l == 0);
   }
-  coarse_correction(h, c, l, s);
   const LevelViewT<V>& cv = c.v[l + 1];
+  restrict_to(v, cv, s, folded_rows(h, l + 1));
+  vcycle(h, c, l + 1, s);
   if (tail) {
     tail_sweeps(tail_post_job(v, cv, 1, h.opt.nu_post, c.symmetric), tail_form(v.maxa), 1, s);
   } else {
@@ -554,22 +554,12 @@ void vcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
   }
 }
 
-// The cycle below level l: its residual restricted, the next level solved.
-template <class V>
-void coarse_correction(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
-  if (l + 2 == h.L.size() && coarse_fuses(h)) {
-    coarse_fused(coarse_job<V>(h, &c.v[l], c.v[l + 1], 1), 1, s);
-    return;
-  }
-  restrict_to(c.v[l], c.v[l + 1], s, folded_rows(h, l + 1));
-  vcycle(h, c, l + 1, s);
-}
-
 // The part of the level-0 V-cycle between pre- and post-smoothing.
 void cycle_inner(Handle& h, hipStream_t s) {
   const Cycle<double>& c = h.plain;
   residual(c.v[0], s, true);
-  coarse_correction(h, c, 0, s);
+  restrict_to(c.v[0], c.v[1], s, folded_rows(h, 1));
+  vcycle(h, c, 1, s);
   prolong_correct(c.v[0], c.v[1], s);
 }
 
@@ -908,8 +898,8 @@ void mvcycle(Handle& h, const Cycle<V>& c, size_t l, hipStream_t s) {
     for (int k = 0; k < h.opt.nu_pre; ++k) mgs_sweep(v, lv, s, false, k == 0 ? skip : 0);
     mresidual(v, s);
   }
-  if (l + 2 == h.L.size() && cv.n <= kCoarseFusedBatch) {
-    coarse_fused(coarse_job<V>(h, &v, cv, kBatch), kBatch, s);
+  if (l + 2 == h.L.size() && coarse_fuses(v.n, cv.n, (int64_t)sizeof(V))) {
+    coarse_solve(coarse_job<V>(h, &v, cv, kBatch), kBatch, s);
   } else {
     mrestrict(v, cv, s);
     mvcycle(h, c, l + 1, s);
@@ -2116,6 +2106,14 @@ int gmg_level_tuning(gmg_handle h, int32_t l, int32_t* out) {
   out[2] = multi && l == 0 ? v.ch : 0;
   out[3] = multi && l > 0 && v.B.nblk > 0 ? 1 : 0;
   out[4] = multi && l == 0 && v.uni && v.A.uw > 0 ? v.A.uw : 0;
+  return GMG_OK;
+}
+
+int gmg_level_routes(gmg_handle h, int32_t l, int32_t* out) {
+  if (!h || !out || l < 0 || l >= (int32_t)h->L.size()) return GMG_INVALID_ARGUMENT;
+  const LevelView& v = h->L[l].view;
+  const int32_t nl = (int32_t)h->L.size();
+  for (int k = 0; k < 2; ++k) out[k] = l + 2 == nl && coarse_fuses(v.n, h->L[l + 1].n, 4 << k) ? 1 : 0;
   return GMG_OK;
 }
 

@@ -162,12 +162,17 @@ constexpr int64_t kTailRows = 4096;  // levels of at most this many rows are swe
 constexpr int kTailT = 512;          // its threads
 constexpr int kTailWMax = 32;        // entries of a row it holds at most
 constexpr int kTailLong = 64;        // the form of levels with longer rows (tail_form)
-constexpr int64_t kCoarseFused = 1024;   // coarsest rows up to which the restriction is fused with the solve
-// coarsest rows up to which that also holds for kBatch vectors of one hierarchy
-// (each workgroup restricts its vector; 226 rows: 10 us against 9 for the restriction
-// and 10.5 for the batched solve; from 513 rows the workgroups take twice the LDS a row)
-constexpr int64_t kCoarseFusedBatch = 512;
-constexpr int64_t kCoarseStaged = 72 * 1024;   // residual bytes it keeps in LDS beside the inverse's columns (at most 73 KiB)
+constexpr int64_t kCoarseAtOnce = 1024;   // coarsest rows up to which a workgroup of the solve takes all columns at once
+// Coarsest rows up to which the batched cycle of one hierarchy restricts into that
+// level in the solve's workgroups, each its whole vector, if the vector's residual
+// fits their LDS beside the inverse's columns (at most 73 KiB).  From 513 rows a workgroup
+// solves eight rows instead of 16, and twice as many restrict.  A batched cycle in float
+// with and without: 242 coarsest rows 74 and 82 us, 494 85 and 102, 549 127 and 113, 965
+// 215 and 156; in double with 80 KB of residual read from memory 552 and 535.  One vector
+// (with one pair of launches for all of it) is never faster so: 291 rows 47.6 us a plain
+// cycle and 46.1, 965 109 and 101, 845 rows of 24-neighbour clouds 656 and 613.
+constexpr int64_t kCoarseFused = 512;
+constexpr int64_t kCoarseStaged = 72 * 1024;
 constexpr int kLaneEntries = 8;      // entries per lane per pass of a lane-parallel row
 
 // A matrix in SELL-64: entry t of row r at ptr[r/64] + 64 t + r%64.
@@ -363,11 +368,12 @@ struct TailJob {
 };
 
 // The coarsest solve, fused with the restriction P^T r when T is set (else b
-// is given); `rows` rows of the solution per workgroup (a power of two).
+// is given); `rows` rows of the solution per workgroup (a power of two, up to
+// kCoarseAtOnce rows).
 template <class V>
 struct CoarseJob {
   int32_t n = 0, rows = 0, stride = 1;
-  int32_t nf = 0, staged = 0;           // length of r; 1: it fits the LDS (kCoarseStaged bytes)
+  int32_t nf = 0;                       // length of r
   const double* M = nullptr;            // the inverse by columns, stride inv_ld(n)
   Sell<V> T;
   const V* r = nullptr;
@@ -769,7 +775,7 @@ void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count,
                   const int32_t* active, hipStream_t s);
 int32_t coarse_rows(int64_t n);
 template <class V>
-void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s);
+void coarse_solve(const CoarseJob<V>& J, int32_t vectors, hipStream_t s);
 void tail_over(const LevelView& v, int32_t nchunk, int32_t* blocks, hipStream_t s);   // blocks past the buffers of every chunk
 template <class V>
 void tail_fill(const LevelView& v, const TailRows<V>& R, hipStream_t s);

@@ -1,7 +1,7 @@
 // The V-cycle on levels with few rows (Alg. 2): all Gauss-Seidel sweeps of one
 // level, the residual after them or the correction before them, in one
-// workgroup; and the restriction into the coarsest level fused with its direct
-// solve.  Grids of these kernels run one workgroup (or row of workgroups) per
+// workgroup; and the direct solve of the coarsest level, in the batched cycle
+// with the restriction into it.  Grids of these kernels run one workgroup (or row of workgroups) per
 // vector: one for the solve, kBatch for the batched forms, whose vectors are
 // interleaved (entry (i, q) at i * stride + q).
 #include <algorithm>
@@ -400,10 +400,10 @@ __global__ void __launch_bounds__(kTailT) k_gtail(const TailJob<V>* __restrict__
 
 // b_c = P^T r (or b_c given, when the job has no P^T) and x_c = A_c^-1 b_c in
 // double: row i is the sum over k ascending of (A_c^-1 e_k)_i b_k.  A workgroup
-// solves J.rows rows of one vector: it restricts the whole vector itself (a
-// few hundred short rows, one lane each: cheaper than a launch to do it once)
-// while its columns of the inverse load, writes their products to LDS, and adds
-// each row's products on one lane, two instructions a term.
+// solves J.rows rows of one vector: in the batched cycle it restricts the whole
+// vector itself while its columns of the inverse load (see kCoarseFused); it writes
+// their products to LDS, and adds each row's products on one lane, two instructions
+// a term.
 constexpr int kCoarseAhead = 16;           // columns read from LDS ahead of their additions
 constexpr int kCoarseM = 16;               // elements of the inverse a thread loads: coarse_rows(n) n / kTailT at most
 constexpr int kCoarseStage = 8;            // elements of the residual a thread has in flight
@@ -460,30 +460,24 @@ __device__ __forceinline__ void coarse_run(const CoarseJob<V>& J, int32_t group,
     a[u] = J.M[(int64_t)(e / R) * ld + min(i0 + (e & (R - 1)), n - 1)];
   }
   if (fused) {
-    // the residual in LDS where it fits: a row gathers some 22 of its entries,
-    // each a cache line of its own from memory
+    // the residual in LDS: a row gathers some 22 of its entries, each a cache line
+    // of its own from memory
     const V* r = J.r + vec;
-    auto restrict_rows = [&](const auto* x, int32_t stride) {
-      for (int32_t i = t; i < n; i += kTailT) {
-        if (i != t) row = sell_row(J.T, i);
-        bc[i] = (double)row_sum_at<kCoarseChunk>(J.T, row, x, stride);
-      }
-    };
-    if (J.staged) {
-      V* rl = reinterpret_cast<V*>(m + up * R);
-      for (int32_t e0 = 0; e0 < J.nf; e0 += kCoarseStage * kTailT) {
-        V v[kCoarseStage];
+    V* rl = reinterpret_cast<V*>(m + up * R);
+    for (int32_t e0 = 0; e0 < J.nf; e0 += kCoarseStage * kTailT) {
+      V v[kCoarseStage];
 #pragma unroll
-        for (int u = 0; u < kCoarseStage; ++u)
-          if (e0 + u * kTailT < J.nf) v[u] = r[(int64_t)min(e0 + u * kTailT + t, J.nf - 1) * K];
+      for (int u = 0; u < kCoarseStage; ++u)
+        if (e0 + u * kTailT < J.nf) v[u] = r[(int64_t)min(e0 + u * kTailT + t, J.nf - 1) * K];
 #pragma unroll
-        for (int u = 0; u < kCoarseStage; ++u)
-          if (e0 + u * kTailT + t < J.nf) rl[e0 + u * kTailT + t] = v[u];
-      }
-      __syncthreads();
-      restrict_rows((const __attribute__((address_space(3))) V*)rl, 1);
-    } else {
-      restrict_rows(r, K);
+      for (int u = 0; u < kCoarseStage; ++u)
+        if (e0 + u * kTailT + t < J.nf) rl[e0 + u * kTailT + t] = v[u];
+    }
+    __syncthreads();
+    const auto* x = (const __attribute__((address_space(3))) V*)rl;
+    for (int32_t i = t; i < n; i += kTailT) {
+      if (i != t) row = sell_row(J.T, i);
+      bc[i] = (double)row_sum_at<kCoarseChunk>(J.T, row, x, 1);
     }
   } else {
     for (int32_t i = t; i < n; i += kTailT) bc[i] = (double)J.b[vec + (int64_t)i * K];
@@ -540,7 +534,7 @@ __global__ void __launch_bounds__(kBlock) k_tail_over(SellView A, const int32_t*
   if ((threadIdx.x & (kWave - 1)) == 0) blocks[q] = max(0, (k.w - kTailWMax) / 8) * k.y;
 }
 
-// The same solve (b given) for coarsest levels of more than kCoarseFused rows, of which
+// The same solve (b given) for coarsest levels of more than kCoarseAtOnce rows, of which
 // a workgroup of coarse_run could take four at most with all their columns: kWideRows
 // rows of a vector a workgroup, the columns in tiles of kWideCols, the next tile's loads
 // in flight while one lane a row adds the products of one.  A direct solve of 1,100 rows
@@ -741,15 +735,14 @@ void gtail_sweeps(const TailJob<V>* jobs, const int32_t* members, int32_t count,
   });
 }
 
-// Rows a workgroup of the coarsest solve of up to kCoarseFused takes: kCoarseM elements
+// Rows a workgroup of the coarsest solve of up to kCoarseAtOnce takes: kCoarseM elements
 // of the inverse a thread, at most 64 KiB in LDS.  More rows per workgroup mean fewer
 // copies of the restriction, fewer mean more load paths.
 int32_t coarse_rows(int64_t n) { return n <= 512 ? 16 : 8; }
 template <class V>
 size_t coarse_lds(const CoarseJob<V>& J) {
-  return (size_t)coarse_up(J.n) * 8 * (1 + J.rows) + (J.staged ? (size_t)J.nf * sizeof(V) : 0);
+  return (size_t)coarse_up(J.n) * 8 * (1 + J.rows) + (J.T.ptr ? (size_t)J.nf * sizeof(V) : 0);
 }
-
 
 template <class F>
 void with_rows(int32_t R, F&& f) {
@@ -760,9 +753,10 @@ void with_rows(int32_t R, F&& f) {
 }
 
 template <class V>
-void coarse_fused(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
-  if (J.n > kCoarseFused) {
-    if (J.T.ptr) throw Error{GMG_DEVICE_ERROR, "coarsest level too large to restrict in its solve"};
+void coarse_solve(const CoarseJob<V>& J, int32_t vectors, hipStream_t s) {
+  if (J.T.ptr && (J.n > kCoarseAtOnce || (int64_t)J.nf * (int64_t)sizeof(V) > kCoarseStaged))
+    throw Error{GMG_DEVICE_ERROR, "level too large to restrict in the coarsest solve"};
+  if (J.n > kCoarseAtOnce) {
     k_coarse_wide<V><<<dim3((J.n + kWideRows - 1) / kWideRows, vectors), kTailT,
                        (size_t)kWideCols * (1 + kWideRows) * 8, s>>>(J);
     return;
@@ -797,7 +791,7 @@ void tail_fill(const LevelView& v, const TailRows<V>& R, hipStream_t s) {
   template void tail_sweeps<V>(const TailJob<V>&, int32_t, int32_t, hipStream_t);                              \
   template void gtail_sweeps<V>(const TailJob<V>*, const int32_t*, int32_t, int32_t, int32_t, size_t, const int32_t*,   \
                                 hipStream_t);                                                                  \
-  template void coarse_fused<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                     \
+  template void coarse_solve<V>(const CoarseJob<V>&, int32_t, hipStream_t);                                     \
   template void tail_fill<V>(const LevelView&, const TailRows<V>&, hipStream_t);
 GMG_INSTANTIATE_TAIL(double)
 GMG_INSTANTIATE_TAIL(float)
