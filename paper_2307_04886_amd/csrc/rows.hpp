@@ -29,11 +29,27 @@ __device__ __forceinline__ SellRow sell_row(const Sell<V>& A, int32_t r) {
   return SellRow{p0 + (r & (kSlice - 1)), A.len[r], (p1 - p0) / kSlice};
 }
 
+// Where the loads of a one-lane row may end: at the slice's width, or, in a slice with
+// a much longer row, some entries past the longest of the wavefront's rows.  (The width
+// is known before the lengths are, and a loop that asks for the lengths as it goes had
+// the compiler issue one gather after the other: 8.6 us a colour for 7.0 below.)
+constexpr int32_t kRowWide = 64;
+__device__ __forceinline__ int32_t row_end(SellRow R) {
+  int32_t end = R.width;
+  if (__ballot(end > kRowWide) != 0) {
+    int32_t e = kRowWide;
+    while (__ballot(R.len > e) != 0) e += kRowWide;
+    end = min(end, e);
+  }
+  return end;
+}
+
 // One lane per row: sum_t val[t] * x[col[t]] in entry order, skipping column
 // `skip`; the row's loads are issued CH at a time before any is consumed.
 // The loads past a row's end stay in the slice (its padding, column 0) at the
-// entry that the other rows of the wavefront read, and only entries t < len
-// enter the sum: all loads of a chunk are in flight together, without branches.
+// entry that the other rows of the wavefront read, up to row_end, and only
+// entries t < len enter the sum: all loads of a chunk are in flight together,
+// without branches.
 // (A load whose short rows each re-read their own last entry touches as many
 // cache lines as there are such rows, and costs the load path that many cycles:
 // on a point cloud of 1,000,003 points, rows of 9-17 entries, a float colour
@@ -41,8 +57,9 @@ __device__ __forceinline__ SellRow sell_row(const Sell<V>& A, int32_t r) {
 template <int CH, class V>
 __device__ __forceinline__ V row_sum_seq(const Sell<V>& A, int32_t r, const V* x, int32_t skip) {
   const SellRow R = sell_row(A, r);
+  const int32_t end = row_end(R);
   V acc = V(0);
-  for (int32_t t0 = 0; t0 < R.width; t0 += CH) {
+  for (int32_t t0 = 0; t0 < end; t0 += CH) {
     int32_t j[CH];
     V v[CH], xv[CH];
 #pragma unroll
@@ -64,8 +81,9 @@ __device__ __forceinline__ V row_sum_seq(const Sell<V>& A, int32_t r, const V* x
 // vectors (x's entry j at j * stride; in LDS or in memory).
 template <int CH, class V, class X>
 __device__ __forceinline__ V row_sum_at(const Sell<V>& A, SellRow R, X x, int32_t stride) {
+  const int32_t end = row_end(R);
   V acc = V(0);
-  for (int32_t t0 = 0; t0 < R.width; t0 += CH) {
+  for (int32_t t0 = 0; t0 < end; t0 += CH) {
     int32_t j[CH];
     V v[CH], xv[CH];
 #pragma unroll
@@ -168,6 +186,12 @@ __device__ __forceinline__ V last_to_first(V v) {
 // lane up (a DPP row shift) and the next lane continues, so the row is summed
 // in entry order with R - 1 cross-lane moves per pass.  A wavefront stops
 // after the pass that covers its longest row.
+//
+// Lanes past the row's end read the slice's padding, which adjacent rows share, unless
+// the slice has a much longer row: there the row's own last entry again.  (5,000 rows,
+// one slice in two with a row of some hundreds of entries: a colour 7.5 us, reading the
+// padding 8.9; without such rows 4.4 us.)
+constexpr int kPadRead = 2 * kLaneEntries;   // entries of padding past a row's end that its lanes read
 template <int R, class V>
 __device__ __forceinline__ V row_sumR(const Sell<V>& A, int32_t r, bool active, const V* x, int32_t skip,
                                       int32_t maxlen) {
@@ -176,17 +200,19 @@ __device__ __forceinline__ V row_sumR(const Sell<V>& A, int32_t r, bool active, 
   SellRow row{};
   if (active) row = sell_row(A, r);
   const int32_t len = row.len;
+  const int32_t last = row.width <= len + kPadRead ? row.width - 1 : len - 1;
   V carry = V(0);
   for (int32_t t0 = 0; t0 < maxlen && __ballot(t0 < len) != 0; t0 += R * K) {
     int32_t j[K];
     V v[K], xv[K], p[K];
     bool ok[K];
     // Branch-free loads, as in row_sum_seq: positions past the slice's width
-    // re-read its last entry (an inactive group: row 0's first).
+    // re-read its last entry (an inactive group: row 0's first), in a slice with a
+    // much longer row those past the row's end the row's own.
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int32_t t = t0 + sub * K + k;
-      const int32_t o = row.base + max(min(t, row.width - 1), 0) * kSlice;
+      const int32_t o = row.base + max(min(t, last), 0) * kSlice;
       j[k] = A.col[o];
       v[k] = A.val[o];
     }

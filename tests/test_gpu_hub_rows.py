@@ -1,0 +1,94 @@
+"""GPU: row sums where a slice of 64 rows has a row much longer than the others (hubs),
+on the finest level and on levels swept by launches of several lanes a row: the
+oracle's bits, and the time of a colour beside that of the same mesh without hubs."""
+import sys
+
+import numpy as np
+import pytest
+
+import synth
+from synth.operators import Problem
+from tests.test_gpu_parity import assert_same_bits
+from tests.test_gpu_pcg import PREC, both
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def stars(nu, nv, spokes, seed=4):
+    """A torus where a few points have `spokes` entries in their row each, among them the
+    first and the last point (the first and last row of a colour, in a slice with the next
+    one's rows)."""
+    import scipy.sparse as sp
+    base = synth.small_torus(nu, nv)
+    n = base.n
+    rng = np.random.default_rng(seed)
+    E = [np.asarray(base.edges, dtype=np.int64)]
+    e = {tuple(x) for x in np.sort(E[0], axis=1)}
+    for c, k in zip([0, n - 1, n // 3, n // 2], spokes):
+        have = sum(c in x for x in e)
+        for j in rng.permutation(n):
+            if have >= k - 1:
+                break
+            x = (min(c, int(j)), max(c, int(j)))
+            if j != c and x not in e:
+                e.add(x)
+                have += 1
+    edges = np.array(sorted(e), dtype=np.int32)
+    W = sp.coo_matrix((-np.ones(len(edges)), (edges[:, 0], edges[:, 1])), shape=(n, n))
+    W = W + W.T
+    A = (W + sp.diags(np.asarray(-W.sum(1)).ravel() + 0.1)).tocsr()
+    A.sort_indices()
+    return Problem("stars", base.points, edges, A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data,
+                   rng.uniform(-1, 1, n))
+
+
+@pytest.mark.parametrize("spokes", [(17, 31, 32, 33), (63, 64, 65, 66), (80, 81, 96, 97), (127, 128, 129, 160)])
+def test_hub_rows(spokes):
+    prob = stars(176, 144, spokes)
+    for opt in (dict(), dict(coarsening_ratio=0.5, block_min_rows=1 << 30)):
+        orc, gpu = both(prob, min_coarse_points=500, **opt)
+        if opt:                              # launches of several lanes a row
+            assert gpu.sizes(1)["n"] > 4096 and gpu.tuning(1)["lanes_A"] >= 4
+        r = np.random.default_rng(12).uniform(-1, 1, prob.n)
+        for precision in ("f64", "f32"):
+            _say(f"[gpu] hub rows {spokes} {opt} {precision}")
+            zo = orc.precondition(r, PREC[precision])
+            zg = gpu.precondition(torch.from_numpy(r).cuda(), precision=precision).cpu().numpy()
+            assert_same_bits(zo, zg, f"{spokes} {precision}")
+            Z = gpu.precondition_batched(torch.from_numpy(np.stack([r, r])).cuda(), precision=precision).cpu().numpy()
+            assert_same_bits(zo, Z[1], f"{spokes} {precision} batched")
+        xo = orc.solve(prob.rhs, tol=0.0, max_iters=2)[0]
+        xg = gpu.solve(torch.from_numpy(prob.rhs).cuda(), tol=0.0, max_iters=2)[0].cpu().numpy()
+        assert_same_bits(xo, xg, f"{spokes}")
+
+
+def colour_us(prob):
+    from paper_2307_04886_amd.binding import default_options, from_problem, timer_start, timer_stop
+    gpu, _ = from_problem(prob, default_options(block_min_rows=1 << 30))
+    assert gpu.num_levels == 3 and gpu.sizes(1)["n"] > 4096
+    b = torch.from_numpy(prob.rhs).cuda()
+    best = float("inf")
+    for _ in range(5):
+        x = torch.zeros_like(b)
+        timer_start("gs_galerkin", 2000)
+        gpu.solve(b, x=x, tol=0.0, max_iters=10)
+        ms, launches, _ = timer_stop()
+        best = min(best, ms * 1e3 / launches)
+    return best
+
+
+def test_hub_slice_time():
+    """A colour of the level below the finest where one slice in two holds a row of some
+    hundreds of entries: its longer chain of passes, 1.6 times the time of a colour
+    without hubs.  With the other rows of these slices reading the padding beside the
+    hub's entries, two or more cache lines for each of their own, it was 2.0 times."""
+    hubs, plain = colour_us(synth.small_hubs(256, 200, hubs=40, spokes=100)), colour_us(synth.small_torus(256, 200))
+    _say(f"[gpu] a colour with hubs {hubs:.2f} us, without {plain:.2f} us")
+    assert hubs < 1.85 * plain
