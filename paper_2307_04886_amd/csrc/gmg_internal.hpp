@@ -759,6 +759,7 @@ void gcoarse(const GCoarseJob<V>* jobs, const GTile* tiles, int32_t ntiles, cons
 // How the rows of a level are held: 8, 16 or kTailWMax entries, or kTailLong where the
 // longest (maxlen) has more
 int32_t tail_form(int32_t maxlen);
+void tail_check();
 template <class V>
 size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc);
 // nu sweeps (the first `skip` colours of the first one done), then the residual

@@ -2278,6 +2278,7 @@ template <class V>
 void tail_layout(Handle& h, const Level& lv, TailRows<V>& R) {
   const LevelView& v = lv.view;
   if (!R.col) {
+    tail_check();
     const int32_t W = std::min<int32_t>(tail_form(v.maxa), kTailWMax);
     R.nchunk = 0;
     for (size_t c = 0; c + 1 < lv.color_ptr.size(); ++c)

@@ -97,9 +97,10 @@ __device__ __forceinline__ void tail_load(const TailJob<V>& J, const V* b, int32
   }
 }
 
-// The iterate's element at byte offset o: it starts the dynamic LDS, at LDS
-// address 0 since these kernels have no other (an address of its own would cost
-// an addition per gather).
+// The iterate's element at byte offset o: it starts the dynamic LDS, at LDS address 0
+// as long as these kernels have no other (tail_check; an address of its own would cost
+// an addition per gather).  A row's value is read by others only across a barrier, which
+// orders these loads behind the stores through lds_raw.
 template <class V>
 __device__ __forceinline__ V lds_at(uint32_t o) {
   return *(const __attribute__((address_space(3))) V*)o;
@@ -672,6 +673,32 @@ void with_tail(int32_t form, int32_t nchunk, F&& f) {
 }  // namespace
 
 int32_t tail_form(int32_t maxlen) { return maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= kTailWMax ? kTailWMax : kTailLong; }
+
+// Throws unless the dynamic LDS of every one-workgroup kernel starts at address 0 (lds_at).
+void tail_check() {
+  static const bool checked = [] {
+    auto at_zero = [](const void* kernel) {
+      hipFuncAttributes a;
+      check_hip(hipFuncGetAttributes(&a, kernel), "attributes of the one-workgroup kernels");
+      if (a.sharedSizeBytes != 0) throw Error{GMG_DEVICE_ERROR, "one-workgroup kernel with static LDS"};
+    };
+    auto all = [&](auto zero) {
+      using V = decltype(zero);
+      for (int32_t form : {8, 16, kTailWMax, kTailLong})
+        for (int32_t nchunk : {1, (int32_t)kTailRows})         // resident and streamed
+          with_tail<V>(form, nchunk, [&](auto WC, auto BC, auto SC, auto LC) {
+            constexpr int W = decltype(WC)::value, NB = decltype(BC)::value;
+            constexpr bool Stream = decltype(SC)::value, Long = decltype(LC)::value;
+            at_zero((const void*)k_tail<V, W, NB, Stream, Long>);
+            at_zero((const void*)k_gtail<V, W, NB, Stream, Long>);
+          });
+    };
+    all(0.0);
+    all(0.0f);
+    return true;
+  }();
+  (void)checked;
+}
 
 template <class V>
 size_t tail_lds_bytes(const TailRows<V>& A, int32_t n, int32_t nc) {
