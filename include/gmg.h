@@ -327,9 +327,13 @@ int gmg_level_sizes(gmg_handle h, int32_t level, int64_t* sizes_host);
 int gmg_level_tuning(gmg_handle h, int32_t level, int32_t* out_host);
 
 /*
- * The forms of the cycles that level l's sizes choose, written to out_host[0..1]:
+ * The forms of the cycles that level l's sizes choose, written to out_host[0..4]:
  *  0 and 1 one if the batched cycle in float (0) and in double (1) restricts from
- *    this level in the coarsest level's solve.
+ *    this level in the coarsest level's solve,
+ *  2 one if the rows are numbered by coarse cell within a colour (the finest level of
+ *    points in an order without locality),
+ *  3 and 4 LDS bytes of the batched block sweep in float (3) and in double (4), 0 where
+ *    the batched cycle sweeps the level by launches per colour class.
  */
 int gmg_level_routes(gmg_handle h, int32_t level, int32_t* out_host);
 

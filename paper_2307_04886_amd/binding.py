@@ -197,11 +197,12 @@ class Hierarchy:
 
     def routes(self, level):
         """gmg_level_routes: the forms of the cycles that the level's sizes choose."""
-        t = np.zeros(2, dtype=np.int32)
+        t = np.zeros(5, dtype=np.int32)
         st = library().gmg_level_routes(self._h, level, t.ctypes.data_as(ctypes.c_void_p))
         if st:
             raise _err(st)
-        return dict(coarse_fused_f32=bool(t[0]), coarse_fused_f64=bool(t[1]))
+        return dict(coarse_fused_f32=bool(t[0]), coarse_fused_f64=bool(t[1]), by_cell=bool(t[2]),
+                    block_lds_f32=int(t[3]), block_lds_f64=int(t[4]))
 
     def export(self, level, what):
         code, dt = EXPORTS[what]

@@ -2114,6 +2114,10 @@ int gmg_level_routes(gmg_handle h, int32_t l, int32_t* out) {
   const LevelView& v = h->L[l].view;
   const int32_t nl = (int32_t)h->L.size();
   for (int k = 0; k < 2; ++k) out[k] = l + 2 == nl && coarse_fuses(v.n, h->L[l + 1].n, 4 << k) ? 1 : 0;
+  out[2] = h->L[l].clustered ? 1 : 0;
+  const bool blocks = l > 0 && l < h->tail_start;
+  out[3] = blocks ? (int32_t)mblock_lds(v.B.with_values((const float*)v.B.elv)) : 0;
+  out[4] = blocks ? (int32_t)mblock_lds(v.B) : 0;
   return GMG_OK;
 }
 

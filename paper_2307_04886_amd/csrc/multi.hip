@@ -161,7 +161,11 @@ __global__ void __launch_bounds__(kBlock) k_mrestrict(Sell<V> T, const V* __rest
 // banks.  A workgroup of 256 threads and some 50 KB (float) leaves three to a
 // compute unit.  13,759 rows in float: 12.4 us a launch against 12 launches of
 // 5.1 us for the block colour's classes (the whole batched solve of a 100K-point
-// torus: 10.8 ms, now 4.0; 24 hierarchies grouped: 71 ms, now 53).
+// torus: 10.8 ms, now 4.0; 24 hierarchies grouped: 71 ms, now 53).  In double a
+// block takes 85 to 156 KB and a compute unit holds one or two, and the blocks are
+// faster all the same: a batched cycle of 100K points 427 us against 762, of 1,048,576
+// 1,630 against 2,483; in float with blocks of 114 and 131 KB 469 against 943 and 1,037
+// against 1,865.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <class V>

@@ -2134,6 +2134,7 @@ void solve_layout(Handle& h, Level& lv, const Level* nx, const int32_t* t_rp, co
     off = (int32_t*)talloc(s, ((size_t)classes * nb + 1) * 4);
     int32_t* order = &lv == &h.L[0] && nx && n > kTailRows ? cluster_order(h, lv, *nx) : nullptr;
     if (order) {                              // (the finest level has neither of the keys above then)
+      lv.clustered = true;
       cls = (int32_t*)talloc(s, (size_t)n * 4);
       k_gather_i32<<<blocks_for(n), kBlock, 0, s>>>(lv.color, order, n, cls);
       key = cls;
