@@ -380,7 +380,7 @@ int gmg_export_level(gmg_handle h, int32_t level, int32_t what, void* host_dst, 
  *  kernel              GMG_TIMER_GS_FINEST: one colour of a Gauss-Seidel sweep on level 0;
  *                      GMG_TIMER_RESIDUAL_FINEST: residual + norm partials on level 0;
  *                      GMG_TIMER_GS_GALERKIN: one colour of a sweep on a Galerkin level
- *                      (solved by separate launches, i.e. above the single-workgroup tail)
+ *                      (swept by separate launches, i.e. of more than 4096 rows)
  *  expected_launches   events to pre-create (more are created on demand)
  * The timed launches of a solve are issued directly instead of from its
  * captured graph.  gmg_timer_stop waits for the recorded events and returns

@@ -296,7 +296,8 @@ __device__ inline bool lfmis_attempt(const int32_t* rp, const int32_t* col, cons
 // lists cost more than the later rounds saved.)
 // 64 holds a triangle mesh's whole 2-ring, repeats included (up to 42); with 32 the
 // points late in the sweep searched again in every round (10,242 points: 15.9 us a
-// round, now 9.3; 24 small meshes 18.5, now 11.5).
+// round, now 9.3; 24 small meshes 18.5, now 11.5).  The lists take 256 bytes a point
+// during the sampling of a level, 67 MB at most.
 constexpr int kConflicts = 64;
 constexpr int64_t kListLevel = 262144;
 

@@ -203,7 +203,9 @@ __global__ void __launch_bounds__(kBlock) k_ig_class(const int32_t* rp, const in
 // every class.  What bounds it is the chain of a round or class, a hundred rows
 // and dependent LDS reads: 16 lanes take a row, an entry each, and join their
 // masks.  (With one thread a row a round took 7,900 cycles and a class 5,000:
-// 1,463 rows 202 us, now 119; 2,374 rows 306 us, now 187.)
+// 1,463 rows 202 us, now 119; 2,374 rows 306 us, now 187.  Rows of more than 64 entries
+// are partitioned by one of their lanes: 400 rows of 106 entries 2,800 us, now 510, and
+// 130 points all coupled among 700 18.4 ms, now 17.0.)
 // Writes the colours and their count.
 constexpr int kSmallColorRows = 4096;
 constexpr int kSmallColorPer = kSmallColorRows / kDrainItems;
@@ -917,6 +919,10 @@ __global__ void __launch_bounds__(kCholT) k_chol_step(double* __restrict__ D, in
 // last row again (loads under conditions had the compiler wait for the newest
 // one, and a pivot loaded as a scalar for all: 450 cycles a step; 194 rows: 88 us,
 // now 43; 513-768 rows: 484, now 237; 1000 rows: 907, now 428).
+//
+// U holds the factor's columns from the diagonal on and nothing before it: row k of U
+// left of column k is not written.  The forward pass reads those entries, within the
+// pivot's own slot, and drops what it makes of them (rows up to k keep their values).
 template <class F, int... Q>
 __device__ __forceinline__ void each_slot_of(F&& f, std::integer_sequence<int, Q...>) {
   (f(std::integral_constant<int, Q>{}), ...);
@@ -1574,7 +1580,8 @@ __global__ void k_local_rows(const int32_t* bpos, const int32_t* blk, const int3
   if (g < n) lpos[g] = bpos[g] - boff[blk[g]];
 }
 
-// mx[0] = most rows, mx[1] = longest halo, mx[2] = widest ELL of any block.
+// mx[0] = most rows, mx[1] = longest halo, mx[2] = widest ELL of any block, mx[3] and
+// mx[4] = most LDS of a block in the batched sweep (mblock_layout), in float and double.
 __global__ void __launch_bounds__(kBlock) k_block_maxima(const int32_t* boff, const int32_t* hoff, const int32_t* bw,
                                                          int32_t nblk, int32_t C, int32_t* mx) {
   int32_t r = 0, hl = 0, w = 0, l4 = 0, l8 = 0;
@@ -2114,8 +2121,8 @@ void solve_layout(Handle& h, Level& lv, const Level* nx, const int32_t* t_rp, co
   int32_t *hist = nullptr, *off = nullptr;
   int32_t* stage = (int32_t*)pinned_staging((size_t)(2 * C + 1) * 4);
   if (lv.color) {
-    // rows sorted by (sweep class, index); on levels small enough for the
-    // single-workgroup tail by (colour, width class, index)
+    // rows sorted by (sweep class, index); on levels swept by one workgroup by
+    // (colour, width class, index)
     const int32_t* key = lv.color;
     int32_t* cls = nullptr;
     int K = 1;
