@@ -1206,17 +1206,25 @@ void build_group_plan(std::vector<Handle*>& H, GroupPlan<V>& P, DeviceTables& dt
     P.order.push_back({GroupPlan<V>::RESTRICT, (int32_t)P.restricts.size()});
     P.restricts.push_back(std::move(rt));
   };
-  // the one-workgroup levels d above the coarsest, one step per form of the rows
+  // the one-workgroup levels d above the coarsest, one step per form of the rows; the
+  // form of long rows takes those of form kTailWMax along, for one launch less
   auto tail_step = [&](int d, bool is_post) {
+    auto form_of = [&](int m) {
+      const int l = (int)H[m]->L.size() - 1 - d;
+      return l < ts[m] ? 0 : tail_form(C[m]->v[l].maxa);
+    };
+    bool any_long = false;
+    for (int m = 0; m < M; ++m) any_long |= form_of(m) == kTailLong;
     for (int32_t form : {8, 16, kTailWMax, kTailLong}) {
       typename GroupPlan<V>::TailStep st;
       st.form = form;
       for (int m = 0; m < M; ++m) {
+        int32_t f = form_of(m);
+        if (f == kTailWMax && any_long) f = kTailLong;
+        if (f != form) continue;
         const Handle& h = *H[m];
         const int l = (int)h.L.size() - 1 - d;
-        if (l < ts[m]) continue;
         const LevelViewT<V>& v = C[m]->v[l];
-        if (tail_form(v.maxa) != form) continue;
         st.jobs.push_back(is_post ? tail_post_job(v, C[m]->v[l + 1], kBatch, h.opt.nu_post, true)
                                   : tail_pre_job(v, kBatch, h.opt.nu_pre, 0));
         st.members.push_back(m);

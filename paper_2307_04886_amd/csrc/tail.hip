@@ -299,7 +299,8 @@ __device__ __forceinline__ void tail_run(const TailJob<V>& J, int32_t vec) {
   if constexpr (Stream)
     for (int32_t i = t; i < J.A.nchunk; i += kTailT) ct[i] = J.A.chunk[i];
   if constexpr (Long)
-    for (int32_t i = t; i < J.A.nchunk; i += kTailT) ot[i] = J.A.over[i];
+    if (J.A.over)                          // (a level of form kTailWMax in a group has none)
+      for (int32_t i = t; i < J.A.nchunk; i += kTailT) ot[i] = J.A.over[i];
   __syncthreads();
   // phases done by the whole workgroup (one barrier ends each)
   int32_t phase = J.skip;

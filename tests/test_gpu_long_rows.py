@@ -84,3 +84,24 @@ def test_long_row_phase_time(n, k):
             best = min(best, (time.perf_counter() - t) / 10)
         _say(f"[gpu] {n} points, k = {k}, {precision}: {best * 1e6:.0f} us a cycle, {best * 1e6 / phases:.2f} us a phase")
         assert best * 1e6 / phases < 4.4
+
+
+def test_long_rows_grouped_one_depth():
+    """Members whose level above the coarsest has rows of up to 8, 16 and 32 entries and
+    longer ones: those of up to 32 go with the longer ones."""
+    from paper_2307_04886_amd.binding import default_options, from_problem, solve_pcg_grouped
+    probs = [synth.small_torus(30, 20), star_of_cliques(400, 14), synth.small_pointcloud(900, 16),
+             synth.small_pointcloud(800, 40), star_of_cliques(300, 30)]
+    hs = [from_problem(p, default_options(max_levels=2, min_coarse_points=60))[0] for p in probs]
+    longest = [int(np.diff(h.export(0, "a_rowptr")).max()) for h in hs]
+    assert longest[0] <= 8 < longest[1] <= 16 < longest[2] <= 32 < longest[3] and 16 < longest[4] <= 32
+    assert all(h.num_levels == 2 for h in hs)
+    Bs = [torch.from_numpy(np.random.default_rng(14).uniform(-1, 1, (2, p.n))).cuda() for p in probs]
+    for precision in ("f64", "f32"):
+        _say(f"[gpu] grouped long rows, one depth {precision}")
+        Xs, infos, sts, _ = solve_pcg_grouped(hs, Bs, precision=precision)
+        for h, B, X, info, st in zip(hs, Bs, Xs, infos, sts):
+            Y, one, s1 = h.solve_pcg_batched(B, precision=precision)
+            assert st == s1 == 0
+            assert_same_bits(Y.cpu().numpy(), X.cpu().numpy(), precision)
+            assert [i.iterations for i in one] == [i.iterations for i in info]
