@@ -173,8 +173,10 @@ constexpr int64_t kCoarseAtOnce = 1024;   // coarsest rows up to which a workgro
 // solves eight rows instead of 16, and twice as many restrict.  A batched cycle in float
 // with and without: 242 coarsest rows 74 and 82 us, 494 85 and 102, 549 127 and 113, 965
 // 215 and 156; in double with 80 KB of residual read from memory 552 and 535.  One vector
-// (with one pair of launches for all of it) is never faster so: 291 rows 47.6 us a plain
-// cycle and 46.1, 965 109 and 101, 845 rows of 24-neighbour clouds 656 and 613.
+// (with one pair of launches for all of it) gains nothing so: ten plain cycles with and
+// without, 201 rows 436 and 420 us, 291 476 and 464, 549 733 and 697, 965 1,120 and 1,011,
+// 845 rows of a cloud with 24 neighbours 6,690 and 6,250; 20 cycles in float from 1% less
+// (291 rows, 653 and 660 us) to 6% more (965 rows).
 constexpr int64_t kCoarseFused = 512;
 constexpr int64_t kCoarseStaged = 72 * 1024;
 constexpr int kLaneEntries = 8;      // entries per lane per pass of a lane-parallel row
