@@ -86,9 +86,9 @@ def colour_us(prob):
 
 def test_hub_slice_time():
     """A colour of the level below the finest where one slice in two holds a row of some
-    hundreds of entries: its longer chain of passes, 1.6 times the time of a colour
+    hundreds of entries: its longer chain of passes, 1.6 to 1.75 times the time of a colour
     without hubs.  With the other rows of these slices reading the padding beside the
-    hub's entries, two or more cache lines for each of their own, it was 2.0 times."""
+    hub's entries, two or more cache lines for each of their own, it was 2.0 to 2.1 times."""
     hubs, plain = colour_us(synth.small_hubs(256, 200, hubs=40, spokes=100)), colour_us(synth.small_torus(256, 200))
     _say(f"[gpu] a colour with hubs {hubs:.2f} us, without {plain:.2f} us")
-    assert hubs < 1.85 * plain
+    assert hubs < 1.92 * plain
